@@ -684,14 +684,15 @@ __device__ __forceinline__ double finish_block(const Buffers& b, int cur, int64_
 }
 
 // LDS of one step workgroup: two copies of the tile of D = Z - b, each in
-// one half of `tile` (its first 7 x 256 doubles double as the record
-// exchange), the table of row sums of D^2, and the reduction scratch.
-// Kernels that run several patch sizes declare it once.
+// one half of the first TILE doubles of `tile` (the first 7 x 256 of them
+// double as the record exchange), then the table of row sums of D^2 (kSqCap
+// doubles); a workgroup whose box does not fit twice keeps one tile in all of
+// it. And the reduction scratch. Kernels that run several patch sizes declare
+// it once.
 template <int TILE>
 struct StepLds {
   static_assert(TILE >= 7 * kBlock, "the tile doubles as the record exchange buffer");
-  __align__(16) double tile[TILE];
-  double sq[kSqCap];
+  __align__(16) double tile[TILE + kSqCap];
   double dsh[4];
   int ish[16];
   int ksh[4];
@@ -730,8 +731,37 @@ __device__ __forceinline__ void patch_lds(const double* __restrict__ p0, int tw,
   }
 }
 
-// The same sums read straight from the frame (workgroups whose patches do
-// not fit one LDS tile); pixels outside the frame read as the background.
+// The same sums, pixel by pixel in the same order, from a tile kept once
+// (row stride tw, no alignment): D as doubles, or the pixels themselves as
+// floats, the background subtracted here (pixels outside the frame are staged
+// as the background, so their D is 0 either way).
+template <int P, class T>
+__device__ __forceinline__ void patch_single(const T* __restrict__ p0, int tw, double bsub,
+                                             const double (&gx)[P], double gy, double by,
+                                             const double* gstep, double& X, double& G2y,
+                                             double& sd2) {
+#pragma unroll 1
+  for (int dy = 0; dy < P; ++dy) {
+    const T* row = p0 + dy * tw;
+    double rd = 0.0;
+#pragma unroll
+    for (int dx = 0; dx < P; ++dx) {
+      double d;
+      if constexpr (sizeof(T) == sizeof(double))
+        d = row[dx];
+      else
+        d = (double)row[dx] - bsub;
+      rd = dx == 0 ? d : fma(d, gx[dx], rd);
+      sd2 = fma(d, d, sd2);
+    }
+    X = fma(gy, rd, X);
+    G2y = fma(gy, gy, G2y);
+    gy *= gstep[dy] * by;
+  }
+}
+
+// The same sums read straight from the frame (waves whose patches fit no LDS
+// tile); pixels outside the frame read as the background.
 template <int P>
 __device__ __forceinline__ void patch_global(const float* __restrict__ obs, int u0, int v0,
                                              int W, int H, double bsub, const double (&gx)[P],
@@ -862,7 +892,7 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
                                           StepLds<TILE>& L) {
   constexpr int h = (P - 1) / 2;
   double* const tile = L.tile;
-  double* const sq = L.sq;
+  double* const sq = L.tile + TILE;
   double* const dsh = L.dsh;
   int* const ish = L.ish;
   const Ctrl* cp = b.ctrl;
@@ -951,10 +981,13 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
     }
   }
   __syncthreads();
-  const int mnx = min(min(ish[0], ish[1]), min(ish[2], ish[3]));
-  const int mxx = max(max(ish[4], ish[5]), max(ish[6], ish[7]));
-  const int mny = min(min(ish[8], ish[9]), min(ish[10], ish[11]));
-  const int mxy = max(max(ish[12], ish[13]), max(ish[14], ish[15]));
+  // the box as scalars: everything that follows from it (sizes, strides, the
+  // choice of path) is then scalar work, off the vector units that bound the
+  // kernel
+  const int mnx = __builtin_amdgcn_readfirstlane(min(min(ish[0], ish[1]), min(ish[2], ish[3])));
+  const int mxx = __builtin_amdgcn_readfirstlane(max(max(ish[4], ish[5]), max(ish[6], ish[7])));
+  const int mny = __builtin_amdgcn_readfirstlane(min(min(ish[8], ish[9]), min(ish[10], ish[11])));
+  const int mxy = __builtin_amdgcn_readfirstlane(max(max(ish[12], ish[13]), max(ish[14], ish[15])));
   // The tile is staged twice, copy B shifted one column left of copy A, each
   // in half of the LDS block with an even row stride: a patch row starting
   // at an even column is read from A, one starting at an odd column from B,
@@ -1005,6 +1038,60 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
                             : 0.0;
       tile[r * ts + c] = dv;
       if (c > 0) tile[kCopy + kOffB + r * ts + c - 1] = dv;
+    }
+  }
+  // A box too large for two copies and the table is kept once, in all of the
+  // workgroup's LDS, as doubles or (twice the pixels) as floats; where even
+  // that is too small (a workgroup whose particles form clusters, as at a jump
+  // of the Z order), each wave keeps its own box in a quarter of it, and a
+  // wave whose box still does not fit reads the frame. The sums are taken in
+  // the frame path's order, so the choice moves no bit. The frame path is
+  // bound by its loads: P^2 bounds-checked ones per particle, 64 addresses
+  // each. Measured: the first frame of 250,007 particles with 25 x 25 patches
+  // from a Gaussian prior 278 -> 67 us; a step of 2^20 particles that lost the
+  // spot (9 x 9) 44.5 -> 34.7 us. Gradient mode keeps the two choices: a third
+  // cost its kernel 2 % (registers) on clouds that never need it.
+  constexpr int kAll = TILE + kSqCap;
+  enum { kFrame, kFloat, kDouble };
+  int single = kFrame;  // uniform in a wave
+  int sx0 = tx0, sy0 = ty0, sw = 0, sbase = 0;
+  if (!GRAD && !use_lds) {
+    int64_t bw = tw64, bh = th64, cap = kAll;
+    int e0 = t, step = 256;
+    if (bw * bh > 2 * (int64_t)kAll) {  // uniform in the workgroup
+      const int x0 = __builtin_amdgcn_readfirstlane(ish[w]);
+      const int x1 = __builtin_amdgcn_readfirstlane(ish[4 + w]);
+      const int y0 = __builtin_amdgcn_readfirstlane(ish[8 + w]);
+      const int y1 = __builtin_amdgcn_readfirstlane(ish[12 + w]);
+      bw = (int64_t)x1 - x0 + P;
+      bh = (int64_t)y1 - y0 + P;
+      cap = kAll / 4;
+      sbase = w * (kAll / 4);
+      sx0 = x0 - h;
+      sy0 = y0 - h;
+      e0 = t & 63;
+      step = 64;
+    }
+    const int64_t np = bw * bh;
+    single = np <= cap ? kDouble : np <= 2 * cap ? kFloat : kFrame;
+    if (single != kFrame) {
+      sw = (int)bw;
+      const int nt = (int)np;
+      const float rcpw = __builtin_amdgcn_rcpf((float)sw);
+      float* const ftile = reinterpret_cast<float*>(tile + sbase);
+      for (int e = e0; e < nt; e += step) {
+        int r = (int)((float)e * rcpw);
+        if (r * sw > e) --r;
+        else if ((r + 1) * sw <= e) ++r;
+        const int v = sy0 + r, u = sx0 + (e - r * sw);
+        const float z = ((unsigned)v < (unsigned)m.H && (unsigned)u < (unsigned)m.W)
+                            ? obs[(int64_t)v * m.W + u]
+                            : (float)m.b;
+        if (single == kDouble)
+          tile[sbase + e] = (double)z - m.b;
+        else
+          ftile[e] = z;
+      }
     }
   }
   __syncthreads();
@@ -1105,6 +1192,13 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
                          by, m.gstep, X, G2y, sd2);
     } else if (use_lds) {
       patch_lds<P, false>(p0, ts, sq, 0, gx, gy0, by, m.gstep, X, G2y, sd2);
+    } else if (single != kFrame) {
+      const int at = (cy - h - sy0) * sw + (cx - h - sx0);  // in the wave's own box
+      if (single == kDouble)
+        patch_single<P>(tile + sbase + at, sw, m.b, gx, gy0, by, m.gstep, X, G2y, sd2);
+      else
+        patch_single<P>(reinterpret_cast<const float*>(tile + sbase) + at, sw, m.b, gx, gy0, by,
+                        m.gstep, X, G2y, sd2);
     } else {
       patch_global<P>(obs, cx - h, cy - h, m.W, m.H, m.b, gx, gy0, by, m.gstep, X, G2y, sd2);
     }
@@ -2905,8 +2999,9 @@ hipError_t launch_spot(const Model& m, const Buffers& b, const float* obs, hipSt
   if constexpr (P <= kFusedMaxP) {
     if (m.shape == 1) return launch_k(k_step_spot<P, 1>, grid, block, s, m, b, obs);
     return launch_k(k_step_spot<P, 0>, grid, block, s, m, b, obs);
+  } else {
+    return launch_k(k_step_spot_wide<P>, grid, block, s, m, b, obs);
   }
-  return launch_k(k_step_spot_wide<P>, grid, block, s, m, b, obs);
 }
 
 inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 1) / block); }
