@@ -57,7 +57,8 @@ constexpr int kFillGridBatch = 2048;  // waves of a batched fill, over all track
 // Batched steps run every patch size up to this one in a single launch (the
 // sizes that fit five waves per SIMD); wider patches launch per size.
 constexpr int kFusedMaxP = 13;
-constexpr int kSortTile = 1024;      // pairs per tile of the radix sort and list scans
+constexpr int kSortTile = 1024;      // pairs per tile of the list scans and of small sorts
+constexpr int64_t kSortLarge = 1 << 22;  // pairs from which the radix sort takes 4096-pair tiles
 // The allocation-free standalone resampler keeps its scratch in a device
 // array of this many bytes, one per device for the life of the process.
 constexpr size_t kStaticScratchBytes = size_t(4) << 20;

@@ -433,7 +433,6 @@ __device__ __forceinline__ void init_body(const Model& m, const Buffers& b, int6
     // Z order: the sort key of draw i; k_init_place writes the states
     const uint4 r0 = draw(m, (uint32_t)i, 0u, kInit, 0u);
     b.zkey0[i] = zorder_key(r0.x, r0.y);
-    b.zval0[i] = (int32_t)i;
     return;
   }
   float xs[5];
@@ -2322,29 +2321,81 @@ __device__ __forceinline__ uint64_t rpa_value(const Buffers& b, int64_t n, int64
 
 // ------------------------------------------------------------ radix sort
 // Stable least-significant-digit sort of (uint32 key, int32 value) pairs,
-// eight bits per pass, in tiles of kSortTile pairs (256 threads x 4 rounds).
-// A pass: the digit's count per tile (k_radix_hist), each digit's row of
-// tile counts turned into exclusive prefixes (k_radix_rowscan, one workgroup
-// per digit), then every pair written to digit start + tile prefix + its
-// rank among the tile's pairs of the same digit in input order
-// (k_radix_scatter). `gate`, when given, skips the pass on steps that do not
+// eight bits per pass, in tiles of T * R pairs (T threads, R rounds; wave w
+// holds the pairs [64 R w, 64 R (w + 1)) of its tile, 64 per round). A pass:
+// the digit's count per tile (k_radix_hist), each digit's row of tile counts
+// turned into exclusive prefixes (k_radix_rowscan, one workgroup per digit),
+// then k_radix_scatter: every pair's rank among its tile's pairs of the same
+// digit in input order, the pairs put in that order in LDS, and written from
+// there to digit start + tile prefix + rank, so that a digit's pairs of a tile
+// leave as one run. `gate`, when given, skips the pass on steps that do not
 // resample.
-__global__ __launch_bounds__(256) void k_radix_hist(const uint32_t* __restrict__ key,
-                                                    int64_t count, int shift,
-                                                    uint32_t* __restrict__ hist, int32_t ntiles,
-                                                    const Ctrl* gate) {
+//
+// The scatter is bound by its writes: a tile's run of one digit is T R / 256
+// pairs long on average. Over 38 M pairs (608 MB a pass) it takes 156 us in
+// tiles of 4096, 192 us in tiles of 2048 and 243-261 us in tiles of 8192 (LDS
+// for one workgroup per CU); written straight from tiles of 1024, 16 bytes to a
+// run, it took 911 us. Below kSortLarge pairs the tiles are 1024 pairs, so that
+// enough workgroups run: 2^20 pairs take 11.0 us against 13.4 us in tiles of
+// 4096 (22 us before), the 304,000 entries of 152,000 groups' lists 135 us for
+// a schedule against 154 us.
+
+// The tile of a workgroup: consecutive tiles, whose runs of a digit are
+// neighbours in the output, go to workgroups of one XCD (workgroups are dealt
+// to the eight in turn), so that a cache line two tiles share is completed in
+// that XCD's L2.
+__device__ __forceinline__ int xcd_tile(int ntiles) {
+  const int x = blockIdx.x & 7, q = ntiles >> 3, r = ntiles & 7;
+  return x * q + min(x, r) + (int)(blockIdx.x >> 3);
+}
+
+// The lanes of this wave whose pair (in) has the digit d.
+__device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool in) {
+  uint64_t peers = __ballot(in);
+#pragma unroll
+  for (int bit = 0; bit < 8; ++bit) {
+    const bool set = (d >> bit) & 1u;
+    const uint64_t bb = __ballot(set);
+    peers &= set ? bb : ~bb;
+  }
+  return peers;
+}
+
+// Adds the digit of every lane's pair to the counts h. A wave whose pairs all
+// hold one digit (the high digits of small values) adds once: 64 atomics on
+// one address would go one after another.
+__device__ __forceinline__ void count_digit(uint32_t* h, uint32_t d, bool in) {
+  const uint64_t all = __ballot(in);
+  if (!all) return;  // uniform
+  const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, __builtin_ctzll(all));
+  if (__ballot(in && d == d0) == all) {
+    if ((threadIdx.x & 63) == 0) atomicAdd(&h[d0], (uint32_t)__popcll(all));
+  } else if (in) {
+    atomicAdd(&h[d], 1u);
+  }
+}
+
+template <int T, int R>
+__global__ __launch_bounds__(T) void k_radix_hist(const uint32_t* __restrict__ key, int64_t count,
+                                                  int shift, uint32_t* __restrict__ hist,
+                                                  int32_t ntiles, const Ctrl* gate) {
   if (gate && !gate->do_resample) return;
   __shared__ uint32_t h[256];
   const int t = threadIdx.x;
-  h[t] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
-  for (int r = 0; r < kSortTile / 256; ++r) {
-    const int64_t j = base + r * 256 + t;
-    if (j < count) atomicAdd(&h[(key[j] >> shift) & 255u], 1u);
+  if (t < 256) h[t] = 0;
+  const int tile = xcd_tile(ntiles);
+  const int64_t base = (int64_t)tile * (T * R);
+  uint32_t k[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t j = base + r * T + t;
+    k[r] = key[min(j, count - 1)];
   }
   __syncthreads();
-  hist[(int64_t)t * ntiles + blockIdx.x] = h[t];
+#pragma unroll
+  for (int r = 0; r < R; ++r) count_digit(h, (k[r] >> shift) & 255u, base + r * T + t < count);
+  __syncthreads();
+  if (t < 256) hist[(int64_t)t * ntiles + tile] = h[t];
 }
 
 __global__ __launch_bounds__(256) void k_radix_rowscan(uint32_t* __restrict__ hist, int32_t ntiles,
@@ -2354,60 +2405,119 @@ __global__ __launch_bounds__(256) void k_radix_rowscan(uint32_t* __restrict__ hi
   __shared__ uint64_t sh[4];
   uint32_t* row = hist + (int64_t)blockIdx.x * ntiles;
   uint64_t carry = 0;
-  for (int32_t i0 = 0; i0 < ntiles; i0 += 256) {
-    const int32_t i = i0 + (int32_t)threadIdx.x;
-    const uint64_t v = i < ntiles ? row[i] : 0;
+  for (int32_t i0 = 0; i0 < ntiles; i0 += 1024) {
+    const int32_t i = i0 + 4 * (int32_t)threadIdx.x;
+    uint32_t v[4];
+    uint64_t s = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = i + q < ntiles ? row[i + q] : 0;
+      s += v[q];
+    }
     uint64_t tot;
-    const uint64_t ex = block_excl_sum(v, sh, &tot);
-    if (i < ntiles) row[i] = (uint32_t)(carry + ex);
+    uint64_t ex = carry + block_excl_sum(s, sh, &tot);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (i + q < ntiles) row[i + q] = (uint32_t)ex;
+      ex += v[q];
+    }
     carry += tot;
   }
   if (threadIdx.x == 0) rowtot[blockIdx.x] = (uint32_t)carry;
 }
 
-__global__ __launch_bounds__(256) void k_radix_scatter(
+// vin null: the values are the pairs' positions. kout null: the keys are not
+// needed any more.
+template <int T, int R>
+__global__ __launch_bounds__(T) void k_radix_scatter(
     const uint32_t* __restrict__ kin, const int32_t* __restrict__ vin, uint32_t* __restrict__ kout,
     int32_t* __restrict__ vout, int64_t count, int shift, const uint32_t* __restrict__ hist,
     const uint32_t* __restrict__ rowtot, int32_t ntiles, const Ctrl* gate) {
+  static_assert(T % 256 == 0, "the first 256 threads take a digit each");
   if (gate && !gate->do_resample) return;
-  __shared__ uint32_t run[256];      // the tile's pairs of each digit in earlier rounds
-  __shared__ uint32_t wcnt[4][256];  // this round's pairs per wave and digit
-  __shared__ uint32_t start[256];    // each digit's first position for this tile
-  __shared__ uint64_t sh[4];
+  constexpr int kWaves = T / 64, kTile = T * R;
+  __shared__ uint32_t skey[kTile];
+  __shared__ int32_t sval[kTile];
+  __shared__ volatile uint32_t wcnt[kWaves][256];  // pairs per wave and digit, then their prefix
+  __shared__ uint32_t lstart[256];  // each digit's first position in the tile's order
+  __shared__ uint32_t gbase[256];   // its first output position, less lstart
+  __shared__ uint32_t sh[2][4];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  uint64_t total;
-  const uint64_t dstart = block_excl_sum((uint64_t)rowtot[t], sh, &total);
-  start[t] = (uint32_t)dstart + hist[(int64_t)t * ntiles + blockIdx.x];
-  run[t] = 0;
-  const int64_t tb = (int64_t)blockIdx.x * kSortTile;
-  for (int r = 0; r < kSortTile / 256; ++r) {
+  const int tile = xcd_tile(ntiles);
+  const int64_t tb = (int64_t)tile * kTile;
+  const int cnt = (int)min((int64_t)kTile, count - tb);
+  const int l0 = 64 * R * w + lane;
+  uint32_t key[R];
+  int32_t val[R];
 #pragma unroll
-    for (int ww = 0; ww < 4; ++ww) wcnt[ww][t] = 0;
-    __syncthreads();
-    const int64_t j = tb + r * 256 + t;
-    const bool in = j < count;
-    const uint32_t key = in ? kin[j] : 0u;
-    const int32_t val = in ? vin[j] : 0;
-    const uint32_t d = (key >> shift) & 255u;
-    // the lanes of this wave holding the same digit
-    uint64_t peers = __ballot(in);
+  for (int r = 0; r < R; ++r) {
+    const int64_t j = tb + min(l0 + 64 * r, cnt - 1);
+    key[r] = kin[j];
+    val[r] = vin ? vin[j] : (int32_t)j;
+  }
+  const uint32_t dtot = t < 256 ? rowtot[t] : 0;
+  const uint32_t before = t < 256 ? hist[(int64_t)t * ntiles + tile] : 0;
 #pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-      const bool set = (d >> bit) & 1u;
-      const uint64_t bb = __ballot(set);
-      peers &= set ? bb : ~bb;
-    }
+  for (int q = 0; q < kWaves * 256 / T; ++q) wcnt[0][q * T + t] = 0;
+  __syncthreads();
+  uint32_t pos[R];  // rank among the wave's pairs of the same digit
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool in = l0 + 64 * r < cnt;
+    const uint32_t d = (key[r] >> shift) & 255u;
+    const uint64_t peers = digit_peers(d, in);
     const uint32_t rank = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
-    if (in && rank == 0) wcnt[w][d] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    if (in) {
-      uint32_t off = start[d] + run[d] + rank;
-      for (int ww = 0; ww < w; ++ww) off += wcnt[ww][d];
-      kout[off] = key;
-      vout[off] = val;
+    const uint32_t old = wcnt[w][d];
+    // (a wave's LDS accesses are served in order: every lane has read the
+    // count before the digit's first lane raises it)
+    __builtin_amdgcn_wave_barrier();
+    if (in && rank == 0) wcnt[w][d] = old + (uint32_t)__popcll(peers);
+    __builtin_amdgcn_wave_barrier();
+    pos[r] = old + rank;
+  }
+  __syncthreads();
+  uint32_t tcnt = 0, li = 0, gi = 0;
+  if (t < 256) {  // whole waves
+#pragma unroll
+    for (int ww = 0; ww < kWaves; ++ww) {
+      const uint32_t c = wcnt[ww][t];
+      wcnt[ww][t] = tcnt;
+      tcnt += c;
     }
-    __syncthreads();
-    run[t] += (wcnt[0][t] + wcnt[1][t]) + (wcnt[2][t] + wcnt[3][t]);
+    li = (uint32_t)wave_scan((int)tcnt, lane, OpAdd());
+    gi = (uint32_t)wave_scan((int)dtot, lane, OpAdd());
+    if (lane == 63) {
+      sh[0][w] = li;
+      sh[1][w] = gi;
+    }
+  }
+  __syncthreads();
+  if (t < 256) {
+    uint32_t l = li - tcnt, g = gi - dtot + before;
+    for (int ww = 0; ww < w; ++ww) {
+      l += sh[0][ww];
+      g += sh[1][ww];
+    }
+    lstart[t] = l;
+    gbase[t] = g - l;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (l0 + 64 * r < cnt) {
+      const uint32_t d = (key[r] >> shift) & 255u;
+      const uint32_t p = lstart[d] + wcnt[w][d] + pos[r];
+      skey[p] = key[r];
+      sval[p] = val[r];
+    }
+  }
+  __syncthreads();
+#pragma unroll 4
+  for (int p = t; p < cnt; p += T) {
+    const uint32_t k = skey[p];
+    const uint32_t o = gbase[(k >> shift) & 255u] + (uint32_t)p;
+    if (kout) kout[o] = k;
+    vout[o] = sval[p];
   }
 }
 
@@ -3122,25 +3232,48 @@ hipError_t static_scratch(void** ptr, size_t* bytes) {
   return hipSuccess;
 }
 
+namespace {
+// The sort of `count` pairs in tiles of T * R: four passes, ping -> pong on
+// even ones and back on odd ones, so the result lands in ping (v0; the last
+// pass leaves the keys unwritten). positions: the values start as the pairs'
+// positions instead of v0.
+template <int T, int R>
+hipError_t radix_sort_tiles(uint32_t* k0, uint32_t* k1, int32_t* v0, int32_t* v1, uint32_t* hist,
+                            uint32_t* row, int64_t count, bool positions, const Ctrl* gate,
+                            hipStream_t s) {
+  static_assert(T * R >= kSortTile, "the digit counts hold a column per kSortTile pairs");
+  const int32_t nt = (int32_t)((count + T * R - 1) / (T * R));
+  hipError_t e = hipSuccess;
+  for (int pass = 0; pass < 4 && e == hipSuccess; ++pass) {
+    const uint32_t* kin = pass & 1 ? k1 : k0;
+    const int32_t* vin = pass & 1 ? v1 : (pass == 0 && positions ? nullptr : v0);
+    uint32_t* kout = pass == 3 ? nullptr : (pass & 1 ? k0 : k1);
+    int32_t* vout = pass & 1 ? v0 : v1;
+    e = launch_k(k_radix_hist<T, R>, dim3((unsigned)nt), dim3(T), s, kin, count, 8 * pass, hist,
+                 nt, gate);
+    if (e == hipSuccess)
+      e = launch_k(k_radix_rowscan, dim3(256), dim3(256), s, hist, nt, row, gate);
+    if (e == hipSuccess)
+      e = launch_k(k_radix_scatter<T, R>, dim3((unsigned)nt), dim3(T), s, kin, vin, kout, vout,
+                   count, 8 * pass, (const uint32_t*)hist, (const uint32_t*)row, nt, gate);
+  }
+  return e;
+}
+
+hipError_t radix_sort(uint32_t* k0, uint32_t* k1, int32_t* v0, int32_t* v1, uint32_t* hist,
+                      uint32_t* row, int64_t count, bool positions, const Ctrl* gate,
+                      hipStream_t s) {
+  if (count >= kSortLarge)
+    return radix_sort_tiles<256, 16>(k0, k1, v0, v1, hist, row, count, positions, gate, s);
+  return radix_sort_tiles<256, 4>(k0, k1, v0, v1, hist, row, count, positions, gate, s);
+}
+}  // namespace
+
 hipError_t launch_init(const Model& m, const Buffers& b, hipStream_t s) {
   hipError_t e = launch_k(k_init, dim3(grid_for(m.n, 256)), dim3(256), s, m, b);
   if (e != hipSuccess || m.init_kind != 3) return e;
   // Z order: sort the keys with their draw indices (stable), then place
-  const int32_t nt = (int32_t)((m.n + kSortTile - 1) / kSortTile);
-  const Ctrl* nogate = nullptr;
-  for (int pass = 0; pass < 4 && e == hipSuccess; ++pass) {
-    const uint32_t* kin = pass & 1 ? b.zkey1 : b.zkey0;
-    const int32_t* vin = pass & 1 ? b.zval1 : b.zval0;
-    uint32_t* kout = pass & 1 ? b.zkey0 : b.zkey1;
-    int32_t* vout = pass & 1 ? b.zval0 : b.zval1;
-    e = launch_k(k_radix_hist, dim3((unsigned)nt), dim3(256), s, kin, m.n, 8 * pass, b.zhist, nt,
-                 nogate);
-    if (e == hipSuccess)
-      e = launch_k(k_radix_rowscan, dim3(256), dim3(256), s, b.zhist, nt, b.zrow, nogate);
-    if (e == hipSuccess)
-      e = launch_k(k_radix_scatter, dim3((unsigned)nt), dim3(256), s, kin, vin, kout, vout, m.n,
-                   8 * pass, (const uint32_t*)b.zhist, (const uint32_t*)b.zrow, nt, nogate);
-  }
+  e = radix_sort(b.zkey0, b.zkey1, b.zval0, b.zval1, b.zhist, b.zrow, m.n, true, nullptr, s);
   if (e == hipSuccess) e = launch_k(k_init_place, dim3(grid_for(m.n, 256)), dim3(256), s, m, b);
   return e;
 }
@@ -3240,23 +3373,9 @@ hipError_t launch_rpa(const Model& m, const Buffers& b, hipStream_t s) {
   hipError_t e = launch_k(k_rpa_first, dim3(grid_for(G + 1, 256)), dim3(256), s, m, b);
   if (e == hipSuccess && m.dlb == 1) {
     const int64_t cnt = 2 * G;
-    const int32_t nt = (int32_t)((cnt + kSortTile - 1) / kSortTile);
     e = launch_k(k_rpa_keys, dim3(grid_for(cnt, 256)), dim3(256), s, m, b);
-    for (int pass = 0; pass < 4 && e == hipSuccess; ++pass) {
-      // ping -> pong on even passes, back on odd ones: the result lands in ping
-      const uint32_t* kin = pass & 1 ? b.rkey1 : b.rkey0;
-      const int32_t* vin = pass & 1 ? b.rval1 : b.rval0;
-      uint32_t* kout = pass & 1 ? b.rkey0 : b.rkey1;
-      int32_t* vout = pass & 1 ? b.rval0 : b.rval1;
-      const Ctrl* gate = b.ctrl;
-      e = launch_k(k_radix_hist, dim3((unsigned)nt), dim3(256), s, kin, cnt, 8 * pass, b.rhist,
-                   nt, gate);
-      if (e == hipSuccess)
-        e = launch_k(k_radix_rowscan, dim3(256), dim3(256), s, b.rhist, nt, b.rrow, gate);
-      if (e == hipSuccess)
-        e = launch_k(k_radix_scatter, dim3((unsigned)nt), dim3(256), s, kin, vin, kout, vout, cnt,
-                     8 * pass, (const uint32_t*)b.rhist, (const uint32_t*)b.rrow, nt, gate);
-    }
+    if (e == hipSuccess)
+      e = radix_sort(b.rkey0, b.rkey1, b.rval0, b.rval1, b.rhist, b.rrow, cnt, false, b.ctrl, s);
   }
   const unsigned nt2 = (unsigned)((G + kSortTile - 1) / kSortTile);
   if (e == hipSuccess) e = launch_k(k_rpa_plan_tiles, dim3(nt2, 2), dim3(256), s, m, b);
@@ -3334,26 +3453,12 @@ hipError_t launch_dlb_schedule(int32_t kind, const int32_t* counts, int32_t G, i
                                int32_t* sched, int32_t cap, int32_t* n_entries, void* scratch,
                                hipStream_t s) {
   const int64_t L = 2 * (int64_t)G;
-  const int32_t nt = (int32_t)((L + kSortTile - 1) / kSortTile);
   DlbScratch d;
   dlb_carve(G, static_cast<char*>(scratch), &d);
-  const Ctrl* nogate = nullptr;
   hipError_t e = launch_k(k_dlb_keys, dim3(grid_for(L, 256)), dim3(256), s, kind, counts, G, n,
                           d.key0, d.val0);
-  for (int pass = 0; pass < 4 && e == hipSuccess; ++pass) {
-    // ping -> pong on even passes, back on odd ones: the lists land in ping
-    const uint32_t* kin = pass & 1 ? d.key1 : d.key0;
-    const int32_t* vin = pass & 1 ? d.val1 : d.val0;
-    uint32_t* kout = pass & 1 ? d.key0 : d.key1;
-    int32_t* vout = pass & 1 ? d.val0 : d.val1;
-    e = launch_k(k_radix_hist, dim3((unsigned)nt), dim3(256), s, kin, L, 8 * pass, d.hist, nt,
-                 nogate);
-    if (e == hipSuccess)
-      e = launch_k(k_radix_rowscan, dim3(256), dim3(256), s, d.hist, nt, d.row, nogate);
-    if (e == hipSuccess)
-      e = launch_k(k_radix_scatter, dim3((unsigned)nt), dim3(256), s, kin, vin, kout, vout, L,
-                   8 * pass, (const uint32_t*)d.hist, (const uint32_t*)d.row, nt, nogate);
-  }
+  if (e == hipSuccess)
+    e = radix_sort(d.key0, d.key1, d.val0, d.val1, d.hist, d.row, L, false, nullptr, s);
   if (e == hipSuccess)
     e = launch_k(k_dlb_values, dim3(grid_for(L, 256)), dim3(256), s, counts, G, n,
                  (const int32_t*)d.val0, d.vals);
