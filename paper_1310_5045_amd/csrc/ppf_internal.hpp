@@ -42,6 +42,12 @@ constexpr double kCdfScale = 0x1p62;    // fixed-point scale of the global CDF
 // Chunk prefixes map 2^44-scaled weights to the 2^62-scaled CDF.
 constexpr double kItemToCdf = 0x1p18;
 
+// Up to this many merge chunks of 256 records (262,144 particles) one
+// workgroup merges them all, side by side, and finishes the step. With more it
+// would take them in turns on one CU: about 2 us of vector work for every four
+// chunks, against one more launch.
+constexpr int kOneMergeChunks = 4;
+
 // Systematic resampling: one wave per segment of kSegBlocks blocks writes the
 // segment's output slots itself when they span at most kCoopTiles tiles of
 // kSlotTile slots; a heavier segment queues its tiles in chunks of

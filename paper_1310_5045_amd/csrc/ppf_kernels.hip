@@ -1355,226 +1355,340 @@ __global__ __launch_bounds__(256) void k_records(Model m, Buffers b,
 // kernel boundary makes the chunk records visible to it: waiting for the
 // last chunk inside one launch costs a device-scope release and acquire in
 // every workgroup, which write back and invalidate that XCD's L2.)
-__device__ __forceinline__ void merge_chunk_body(const Model& m, const Buffers& b, int standalone,
-                                                 int64_t ch) {
-  __shared__ double dsh[4];
-  __shared__ double nsh[4 * 7];
-  __shared__ double gsh[4 * kNGrad];
-  __shared__ uint64_t ush[4];
-  const Ctrl* c = b.ctrl;
-  const int t = threadIdx.x;
-  const int which = standalone ? 0 : (c->cur ^ 1);  // the records this step wrote
-  const double* R = which ? b.R1 : b.R0;
-  const int64_t lo = ch * b.chunk, hi = min(b.nb, lo + b.chunk);
-  const int per = (int)(b.chunk / 256);
-  const int64_t j0 = lo + (int64_t)t * per;
+//
+// These launches are latency: kernel arguments, the control block, the
+// records, then a chain of reductions and exps on a few waves, 3.5-5 us each.
+// So a record is loaded from both buffers before the control block has told
+// which one counts, a thread keeps its record in registers, and one wave holds
+// up to 64 chunks and takes the scalar results in every lane (no broadcast, one
+// division for the five means). With at most kOneMergeChunks chunks of 256
+// records one launch does both, the chunks side by side in one workgroup and
+// their records in LDS: 4096 particles 3.5 + 4.9 us in two launches, 5.5 us in
+// one; 100,003 3.9 + 4.8 and 6.0 us; 262,144 with derivatives 5.4 + 6.8 and 11.0
+// us (a gap between two launches is another 1 us or so).
+struct MergeSh {
+  double mx[4];
+  uint64_t q[4];
+  double sums[4 * 7];
+  double grads[4 * kNGrad];
+};
 
-  double mx = -INFINITY;
-  for (int q = 0; q < per; ++q) {
-    const int64_t j = j0 + q;
-    if (j < hi) mx = fmax(mx, R[j * kRec]);
-  }
-  const double Mc = block_reduce(mx, dsh, OpMax());
-  uint64_t qs = 0;
-  double s2 = 0.0, ex[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  double gs[kNGrad] = {};
-  for (int q = 0; q < per; ++q) {
-    const int64_t j = j0 + q;
-    if (j < hi) {
-      const double* r = R + j * kRec;
-      const double f = (r[0] == -INFINITY) ? 0.0 : exp(r[0] - Mc);
-      qs += (uint64_t)rint(r[1] * f);
-      s2 += r[2] * (f * f);
+// Wave results combined over the four waves w of a 256-thread group (one wave
+// alone when WAVES is 1: the absent ones would add zeros). Each sh is used
+// once.
+template <int WAVES, class T, class Op>
+__device__ __forceinline__ T group_reduce(T v, T* sh, int w, Op op) {
+  v = wave_reduce(v, 0, op);
+  if (WAVES == 1) return v;
+  if ((threadIdx.x & 63) == 0) sh[w] = v;
+  __syncthreads();
+  return op(op(sh[0], sh[1]), op(sh[2], sh[3]));
+}
+template <int WAVES, int K>
+__device__ __forceinline__ void group_sum_n(double (&v)[K], double* sh, int w) {
 #pragma unroll
-      for (int d = 0; d < 5; ++d) ex[d] += r[3 + d] * f;
+  for (int k = 0; k < K; ++k) v[k] = wave_reduce_last(v[k], OpAdd(), 0.0);
+  if (WAVES == 1) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = readlane(v[k], 63);
+    return;
+  }
+  if ((threadIdx.x & 63) == 63) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) sh[w * K + k] = v[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = (sh[k] + sh[K + k]) + (sh[2 * K + k] + sh[3 * K + k]);
+}
+template <int WAVES>
+__device__ __forceinline__ uint64_t group_excl_sum(uint64_t v, uint64_t* sh, int w,
+                                                   uint64_t* total) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t inc = wave_scan(v, lane, OpAdd());
+  if (WAVES == 1) {
+    *total = readlane(inc, 63);
+    return inc - v;
+  }
+  if (lane == 63) sh[w] = inc;
+  __syncthreads();
+  uint64_t before = 0;
+  for (int j = 0; j < w; ++j) before += sh[j];
+  *total = sh[0] + sh[1] + sh[2] + sh[3];
+  return before + inc - v;
+}
+
+// Merges chunk ch (records past the last chunk's end contribute nothing) with
+// the 256 threads t of a group whose waves are w: the blocks' prefixes, and by
+// thread 0 the chunk record and derivative record. ONE: a chunk is 256 records,
+// one per thread.
+template <bool ONE>
+__device__ __forceinline__ void merge_chunk_body(const Model& m, const Buffers& b, int standalone,
+                                                 int64_t ch, int t, int w, MergeSh& sh, double* cr,
+                                                 double* crg) {
+  const int64_t lo = ch * b.chunk, hi = min(b.nb, lo + b.chunk);
+  const int per = ONE ? 1 : (int)(b.chunk / 256);
+  const int64_t j0 = lo + (int64_t)t * per;
+  constexpr int kPer = ONE ? 1 : 8;  // records per thread at most
+
+  double rec[kRec], rec1[kRec];  // ONE: the thread's record, from either buffer
+  if (ONE) {
+    const int64_t j = min(j0, b.nb - 1) * kRec;
+#pragma unroll
+    for (int d = 0; d < kRec; ++d) rec[d] = b.R0[j + d];
+    if (!standalone)
+#pragma unroll
+      for (int d = 0; d < kRec; ++d) rec1[d] = b.R1[j + d];
+  }
+  const int which = standalone ? 0 : (b.ctrl->cur ^ 1);  // the records this step wrote
+  const double* R = which ? b.R1 : b.R0;
+  double mx = -INFINITY;
+  if (ONE) {
+    if (which)
+#pragma unroll
+      for (int d = 0; d < kRec; ++d) rec[d] = rec1[d];
+    if (j0 < hi) mx = rec[0];
+  } else {
+    for (int q = 0; q < per; ++q) {
+      const int64_t j = j0 + q;
+      if (j < hi) mx = fmax(mx, R[j * kRec]);
+    }
+  }
+  const double Mc = group_reduce<4>(mx, sh.mx, w, OpMax());
+  uint64_t qs = 0, qj[kPer];
+  double sums[6] = {};  // sum E^2, then sum E x
+  double gs[kNGrad] = {};
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int64_t j = j0 + q;
+    qj[q] = 0;
+    if (q < per && j < hi) {
+      const double* r = ONE ? rec : R + j * kRec;
+      const double f = (r[0] == -INFINITY) ? 0.0 : exp(r[0] - Mc);
+      qj[q] = (uint64_t)rint(r[1] * f);
+      qs += qj[q];
+      sums[0] += r[2] * (f * f);
+#pragma unroll
+      for (int d = 0; d < 5; ++d) sums[1 + d] += r[3 + d] * f;
       if (m.grad && f != 0.0)
 #pragma unroll
         for (int d = 0; d < kNGrad; ++d) gs[d] += b.RG[j * kNGrad + d] * f;
     }
   }
   uint64_t qtot;
-  uint64_t run = block_excl_sum(qs, ush, &qtot);
-  for (int q = 0; q < per; ++q) {
+  uint64_t run = group_excl_sum<4>(qs, sh.q, w, &qtot);
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
     const int64_t j = j0 + q;
-    if (j < hi) {
-      const double* r = R + j * kRec;
-      const double f = (r[0] == -INFINITY) ? 0.0 : exp(r[0] - Mc);
+    if (q < per && j < hi) {
       b.pfx[j] = run;
-      run += (uint64_t)rint(r[1] * f);
+      run += qj[q];
     }
   }
-  double sums[6] = {s2, ex[0], ex[1], ex[2], ex[3], ex[4]};
-  block_sum_n(sums, nsh);
+  group_sum_n<4>(sums, sh.sums, w);
   if (t == 0) {
-    double* cr = b.CR + ch * kRec;
     cr[0] = Mc;
     cr[1] = __longlong_as_double((long long)qtot);
 #pragma unroll
     for (int d = 0; d < 6; ++d) cr[2 + d] = sums[d];
   }
   if (m.grad) {
-    block_sum_n<kNGrad>(gs, gsh);
+    group_sum_n<4, kNGrad>(gs, sh.grads, w);
     if (t == 0)
 #pragma unroll
-      for (int d = 0; d < kNGrad; ++d) b.CRG[ch * kNGrad + d] = gs[d];
+      for (int d = 0; d < kNGrad; ++d) crg[d] = gs[d];
   }
 }
 
+// By one workgroup of WAVES waves holding the chunks (at most 64 with one
+// wave); CR, CRG: the chunk records, in global memory or in LDS.
+template <int WAVES>
 __device__ __forceinline__ void merge_final_body(const Model& m, const Buffers& b, int standalone,
-                                                 double u_given) {
-  __shared__ double dsh[4];
-  __shared__ double nsh[4 * 7];
-  __shared__ double gsh[4 * kNGrad];
+                                                 double u_given, const double* CR,
+                                                 const double* CRG, MergeSh& sh) {
   __shared__ uint64_t ush[4];
-  __shared__ int sh_pre;
-  __shared__ double sh_delta;
   Ctrl* c = b.ctrl;
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, w = WAVES == 1 ? 0 : wave_index();
   const int64_t nch = b.nch;
-  const int per2 = (int)((nch + 255) / 256);
+  const int per2 = WAVES == 1 ? 1 : (int)((nch + 255) / 256);
   const int64_t c0 = (int64_t)t * per2;
-  const double* CRd = b.CR;
-  auto ld = [&](int64_t idx) { return CRd[idx]; };
+  // the control block's old values, loaded with the records (every thread is
+  // past these loads at the barriers or reductions before the stores below)
+  const int64_t k = (standalone ? 0 : c->k) + 1;
+  const int cur = standalone ? 0 : c->cur;
+  const double cum = c->cum, delta_ref = c->delta_ref;
+  const int rolled = c->rolled_back;
+  const int gl = min(max(t - 16, 0), kNGrad - 1);  // threads 16..24: a derivative each
+  const double gcum = m.grad ? c->grad_cum[gl] : 0.0;
+  double r1[kRec];  // per2 == 1: the thread's chunk record
+  const bool one = per2 == 1;
+  if (one) {
+    const double* r = CR + min(c0, nch - 1) * kRec;
+#pragma unroll
+    for (int d = 0; d < kRec; ++d) r1[d] = r[d];
+  }
+  auto field = [&](int64_t cc, int d) { return one ? r1[d] : CR[cc * kRec + d]; };
   double mx2 = -INFINITY;
   for (int q = 0; q < per2; ++q) {
     const int64_t cc = c0 + q;
-    if (cc < nch) mx2 = fmax(mx2, ld(cc * kRec));
+    if (cc < nch) mx2 = fmax(mx2, field(cc, 0));
   }
-  const double M = block_reduce(mx2, dsh, OpMax());
-  double S = 0.0, S2 = 0.0, E[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  const double M = group_reduce<WAVES>(mx2, sh.mx, w, OpMax());
+  double tot7[7] = {};  // S, sum E^2, sum E x
+  double G[kNGrad] = {};
   for (int q = 0; q < per2; ++q) {
     const int64_t cc = c0 + q;
     if (cc < nch) {
-      const double mc = ld(cc * kRec);
+      const double mc = field(cc, 0);
       const double f = (mc == -INFINITY) ? 0.0 : exp(mc - M);
-      const uint64_t Q = (uint64_t)__double_as_longlong(ld(cc * kRec + 1));
-      S += (double)Q * f;
-      S2 += ld(cc * kRec + 2) * (f * f);
+      const uint64_t Q = (uint64_t)__double_as_longlong(field(cc, 1));
+      tot7[0] += (double)Q * f;
+      tot7[1] += field(cc, 2) * (f * f);
 #pragma unroll
-      for (int d = 0; d < 5; ++d) E[d] += ld(cc * kRec + 3 + d) * f;
+      for (int d = 0; d < 5; ++d) tot7[2 + d] += field(cc, 3 + d) * f;
+      if (m.grad && mc != -INFINITY)
+#pragma unroll
+        for (int d = 0; d < kNGrad; ++d) G[d] += CRG[cc * kNGrad + d] * f;
     }
   }
-  {
-    double tot7[7] = {S, S2, E[0], E[1], E[2], E[3], E[4]};
-    block_sum_n(tot7, nsh);
-    S = tot7[0] * (1.0 / kItemScale);
-    S2 = tot7[1];
+  group_sum_n<WAVES>(tot7, sh.sums, w);
+  const double S = tot7[0] * (1.0 / kItemScale), S2 = tot7[1];
+  if (m.grad) group_sum_n<WAVES, kNGrad>(G, sh.grads, w);
+
+  // every thread takes the step's scalars
+  bool ok = isfinite(M) && isfinite(S) && S > 0.0 && isfinite(S2);
 #pragma unroll
-    for (int d = 0; d < 5; ++d) E[d] = tot7[2 + d];
-  }
-  double G[kNGrad] = {};
-  if (m.grad) {
-    for (int q = 0; q < per2; ++q) {
-      const int64_t cc = c0 + q;
-      if (cc < nch) {
-        const double mc = ld(cc * kRec);
-        if (mc != -INFINITY) {
-          const double f = exp(mc - M);
+  for (int d = 0; d < 5; ++d) ok = ok && isfinite(tot7[2 + d]);
 #pragma unroll
-          for (int d = 0; d < kNGrad; ++d) G[d] += b.CRG[cc * kNGrad + d] * f;
-        }
-      }
-    }
-    block_sum_n<kNGrad>(G, gsh);
-  }
-  if (t == 0) {
-    bool ok = isfinite(M) && isfinite(S) && S > 0.0 && isfinite(S2);
-#pragma unroll
-    for (int d = 0; d < 5; ++d) ok = ok && isfinite(E[d]);
-#pragma unroll
-    for (int d = 0; d < kNGrad; ++d) ok = ok && isfinite(G[d]);
-    int pre = 0;
-    if (standalone) {
+  for (int d = 0; d < kNGrad; ++d) ok = ok && isfinite(G[d]);
+  const double logS = log(S);
+  const double delta = ok ? M + logS : 0.0;
+  const double ess = S * S / S2;
+  const bool res = standalone ? ok : ok && ess < m.thr;
+  if (standalone) {
+    if (t == 0) {
       c->cur = 0;
-      c->delta = ok ? M + log(S) : 0.0;
+      c->delta = delta;
       c->u = u_given;
       c->do_resample = ok ? 1 : 0;
       c->k = 0;
-      pre = ok ? 1 : 0;
-    } else if (ok) {
-      const int64_t k = c->k + 1;
-      const double ess = S * S / S2;
-      const double logS = log(S);
-      const bool res = ess < m.thr;
-      c->k = k;
-      c->cur ^= 1;
-      c->m = M;
-      c->log_sum = logS;
-      c->ess = ess;
-      c->delta = M + logS;
-      c->cum += M + logS;
+      c->heavy_count = 0;
+    }
+  } else if (ok) {
+    if (t < 64) {
+      // threads 1..5 a mean, threads 16..24 a derivative: one division
+      double e = tot7[2];
 #pragma unroll
-      for (int d = 0; d < 5; ++d) c->mean[d] = E[d] / S;
+      for (int d = 1; d < 5; ++d) e = t == 1 + d ? tot7[2 + d] : e;
       if (m.grad)
 #pragma unroll
-        for (int d = 0; d < kNGrad; ++d) {
-          c->grad_last[d] = G[d] / S;
-          c->grad_cum[d] += G[d] / S;
-        }
-      c->resampled = res ? 1 : 0;
-      c->do_resample = res ? 1 : 0;
-      c->mode = res ? (m.arna ? kModeArna : (m.group > 0 ? kModeRna : kModeSys)) : kModeNone;
-      if (m.arna) {
-        // the object is lost when this increment falls well below that of
-        // the last frame that tracked it; each loss keys a new ring order
-        const double inc = M + logS;
-        const bool lost = inc < c->delta_ref - m.arna_drop;
-        if (lost)
-          c->ring_key = k;
-        else
-          c->delta_ref = inc;
-        c->lost = lost ? 1 : 0;
-        c->arna_tracking = 0;  // counted by k_arna_local
-        c->arna_moved = 0;     // set by k_arna_exchange
+        for (int d = 0; d < kNGrad; ++d) e = t == 16 + d ? G[d] : e;
+      e /= S;
+      if (t >= 1 && t < 6) c->mean[t - 1] = e;
+      if (m.grad && t >= 16 && t < 16 + kNGrad) {
+        c->grad_last[t - 16] = e;
+        c->grad_cum[t - 16] = gcum + e;
       }
       const uint4 rr = draw(m, 0u, (uint32_t)k, kResample, 0u);
-      c->u = u53(rr.x, rr.y);
-      pre = (res && m.group == 0) ? 1 : 0;
-    } else {
-      c->rolled_back += 1;
-      c->do_resample = 0;
+      if (t == 0) {
+        c->k = k;
+        c->cur = cur ^ 1;
+        c->m = M;
+        c->log_sum = logS;
+        c->ess = ess;
+        c->delta = delta;
+        c->cum = cum + delta;
+        c->resampled = res ? 1 : 0;
+        c->do_resample = res ? 1 : 0;
+        c->mode = res ? (m.arna ? kModeArna : (m.group > 0 ? kModeRna : kModeSys)) : kModeNone;
+        c->heavy_count = 0;
+        c->u = u53(rr.x, rr.y);
+        if (m.arna) {
+          // the object is lost when this increment falls well below that of
+          // the last frame that tracked it; each loss keys a new ring order
+          const bool lost = delta < delta_ref - m.arna_drop;
+          if (lost)
+            c->ring_key = k;
+          else
+            c->delta_ref = delta;
+          c->lost = lost ? 1 : 0;
+          c->arna_tracking = 0;  // counted by k_arna_local
+          c->arna_moved = 0;     // set by k_arna_exchange
+        }
+      }
     }
-    sh_pre = pre;
-    sh_delta = c->delta;
+  } else if (t == 0) {
+    c->rolled_back = rolled + 1;
+    c->do_resample = 0;
     c->heavy_count = 0;
   }
-  __syncthreads();
-  if (!sh_pre) return;
+  if (!res || (!standalone && m.group > 0)) return;  // uniform
   // chunk prefixes of the fixed-point CDF (2^62 = total weight)
-  const double delta = sh_delta;
-  uint64_t wsum = 0;
-  for (int q = 0; q < per2; ++q) {
-    const int64_t cc = c0 + q;
-    if (cc < nch) {
-      const double mc = ld(cc * kRec);
-      const double phi = (mc == -INFINITY) ? 0.0 : exp(mc - delta) * kItemToCdf;
-      const uint64_t Q = (uint64_t)__double_as_longlong(ld(cc * kRec + 1));
-      wsum += (uint64_t)rint((double)Q * phi);
-    }
-  }
+  auto weight = [&](int64_t cc, double* phi) {
+    const double mc = field(cc, 0);
+    *phi = (mc == -INFINITY) ? 0.0 : exp(mc - delta) * kItemToCdf;
+    return (uint64_t)rint((double)(uint64_t)__double_as_longlong(field(cc, 1)) * *phi);
+  };
+  uint64_t wsum = 0, wq = 0;
+  double phi = 0.0;
+  for (int q = 0; q < per2; ++q)
+    if (c0 + q < nch) wsum += (wq = weight(c0 + q, &phi));
   uint64_t tot;
-  uint64_t pre = block_excl_sum(wsum, ush, &tot);
+  uint64_t pre = group_excl_sum<WAVES>(wsum, ush, w, &tot);
   for (int q = 0; q < per2; ++q) {
     const int64_t cc = c0 + q;
     if (cc < nch) {
-      const double mc = ld(cc * kRec);
-      const double phi = (mc == -INFINITY) ? 0.0 : exp(mc - delta) * kItemToCdf;
-      const uint64_t Q = (uint64_t)__double_as_longlong(ld(cc * kRec + 1));
+      if (!one) wq = weight(cc, &phi);
       b.cpre[cc].P = pre;
       b.cpre[cc].phi = phi;
-      pre += (uint64_t)rint((double)Q * phi);
+      pre += wq;
     }
   }
   if (t == 0) c->total = tot;
 }
 
-__global__ __launch_bounds__(256) void k_merge(Model m, Buffers b, int standalone) {
-  merge_chunk_body(m, b, standalone, blockIdx.x);
+__device__ __forceinline__ void merge_chunk(const Model& m, const Buffers& b, int standalone,
+                                            int64_t ch) {
+  __shared__ MergeSh sh;
+  double* cr = b.CR + ch * kRec;
+  double* crg = b.CRG + ch * kNGrad;
+  const int t = threadIdx.x, w = wave_index();
+  if (b.chunk == 256)
+    merge_chunk_body<true>(m, b, standalone, ch, t, w, sh, cr, crg);
+  else
+    merge_chunk_body<false>(m, b, standalone, ch, t, w, sh, cr, crg);
 }
 
-__global__ __launch_bounds__(256) void k_merge_final(Model m, Buffers b, int standalone,
-                                                     double u_given) {
-  merge_final_body(m, b, standalone, u_given);
+template <int WAVES>
+__device__ __forceinline__ void merge_final(const Model& m, const Buffers& b, int standalone,
+                                            double u_given) {
+  __shared__ MergeSh sh;
+  merge_final_body<WAVES>(m, b, standalone, u_given, b.CR, b.CRG, sh);
+}
+
+__global__ __launch_bounds__(256) void k_merge(Model m, Buffers b, int standalone) {
+  merge_chunk(m, b, standalone, blockIdx.x);
+}
+
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_merge_final(Model m, Buffers b, int standalone,
+                                                            double u_given) {
+  merge_final<WAVES>(m, b, standalone, u_given);
+}
+
+// Both, for at most kOneMergeChunks chunks of 256 records: 256 threads to a
+// chunk, then the first wave (the others would only take issue slots from it).
+__global__ __launch_bounds__(256 * kOneMergeChunks) void k_merge_one(Model m, Buffers b,
+                                                                     int standalone,
+                                                                     double u_given) {
+  __shared__ MergeSh sh[kOneMergeChunks];
+  __shared__ double cr[kOneMergeChunks * kRec], crg[kOneMergeChunks * kNGrad];
+  const int sub = wave_index() >> 2;
+  merge_chunk_body<true>(m, b, standalone, sub, threadIdx.x & 255, wave_index() & 3, sh[sub],
+                         cr + sub * kRec, crg + sub * kNGrad);
+  __syncthreads();
+  if (wave_index() != 0) return;
+  merge_final_body<1>(m, b, standalone, u_given, cr, crg, sh[0]);
 }
 
 // --------------------------------------------------- systematic resampling
@@ -2948,13 +3062,13 @@ __global__ __launch_bounds__(256) void k_merge_batch(const Model* __restrict__ m
                                                      const Buffers* __restrict__ bs,
                                                      const BatchItem* __restrict__ items) {
   const BatchItem it = items[blockIdx.x];
-  merge_chunk_body(ms[it.track], bs[it.track], 0, it.idx);
+  merge_chunk(ms[it.track], bs[it.track], 0, it.idx);
 }
 
 // One workgroup per track.
 __global__ __launch_bounds__(256) void k_merge_final_batch(const Model* __restrict__ ms,
                                                            const Buffers* __restrict__ bs) {
-  merge_final_body(ms[blockIdx.x], bs[blockIdx.x], 0, 0.0);
+  merge_final<4>(ms[blockIdx.x], bs[blockIdx.x], 0, 0.0);
 }
 
 __global__ __launch_bounds__(kWave) void k_anc_batch(const Model* __restrict__ ms,
@@ -3484,9 +3598,13 @@ hipError_t launch_dlb_schedule(int32_t kind, const int32_t* counts, int32_t G, i
 
 hipError_t launch_merge(const Model& m, const Buffers& b, int standalone, double u_given,
                         hipStream_t s) {
+  if (b.nch <= kOneMergeChunks && b.chunk == 256)
+    return launch_k(k_merge_one, dim3(1), dim3(256 * (unsigned)b.nch), s, m, b, standalone,
+                    u_given);
   const hipError_t e = launch_k(k_merge, dim3((unsigned)b.nch), dim3(256), s, m, b, standalone);
   if (e != hipSuccess) return e;
-  return launch_k(k_merge_final, dim3(1), dim3(256), s, m, b, standalone, u_given);
+  if (b.nch <= 64) return launch_k(k_merge_final<1>, dim3(1), dim3(64), s, m, b, standalone, u_given);
+  return launch_k(k_merge_final<4>, dim3(1), dim3(256), s, m, b, standalone, u_given);
 }
 
 hipError_t launch_anc(const Model& m, const Buffers& b, const WeightSrc& w, hipStream_t s) {
