@@ -584,10 +584,7 @@ int enqueue_step(ppf_handle h, const float* obs_dev) {
     return h->run(kKRna, [&] { return ppf::launch_rna_groups(h->m, h->b, h->stream); });
   if (h->p.resample == PPF_RESAMPLE_ARNA)
     return h->run(kKRna, [&] { return ppf::launch_arna(h->m, h->b, h->stream); });
-  rc = h->run(kKResample, [&] {
-    const hipError_t e = ppf::launch_anc(h->m, h->b, w, h->stream);
-    return e != hipSuccess ? e : ppf::launch_fill(h->m, h->b, w, h->stream);
-  });
+  rc = h->run(kKResample, [&] { return ppf::launch_anc(h->m, h->b, w, h->stream); });
   if (rc || !h->m.rpa) return rc;
   return h->run(kKRpa, [&] { return ppf::launch_rpa(h->m, h->b, h->stream); });
 }
@@ -866,7 +863,6 @@ int ppf_resample_systematic(const float* logw_dev, int64_t n, double u, int32_t*
   hipError_t e = ppf::launch_records(m, b, logw_dev, s);
   if (e == hipSuccess) e = ppf::launch_merge(m, b, 1, u, s);
   if (e == hipSuccess) e = ppf::launch_anc(m, b, w, s);
-  if (e == hipSuccess) e = ppf::launch_fill(m, b, w, s);
   return e == hipSuccess ? PPF_OK : PPF_EDEVICE;
 }
 

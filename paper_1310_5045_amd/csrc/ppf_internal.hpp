@@ -59,6 +59,10 @@ constexpr int kSlotTile = kSegItems;  // slots per LDS tile of the segment's wri
 constexpr int kCoopTiles = 4;
 constexpr int kChunkTiles = 2;
 constexpr int kFillGrid = 4096;
+// Up to kWave kHelpPerLane segments (2^20 particles) one launch does both, with
+// kHelpWaves waves that find and write the heavy segments.
+constexpr int kHelpPerLane = 16;
+constexpr int kHelpWaves = 512;
 constexpr int kFillGridBatch = 2048;  // waves of a batched fill, over all tracks' queues
 // Batched steps run every patch size up to this one in a single launch (the
 // sizes that fit five waves per SIMD); wider patches launch per size.
@@ -250,8 +254,8 @@ hipError_t launch_init(const Model& m, const Buffers& b, hipStream_t s);
 hipError_t launch_step(const Model& m, const Buffers& b, const float* obs, hipStream_t s);
 hipError_t launch_merge(const Model& m, const Buffers& b, int standalone, double u_given,
                         hipStream_t s);
+// The systematic resampling pass: the segments, and the heavy ones' tiles.
 hipError_t launch_anc(const Model& m, const Buffers& b, const WeightSrc& w, hipStream_t s);
-hipError_t launch_fill(const Model& m, const Buffers& b, const WeightSrc& w, hipStream_t s);
 hipError_t launch_rna(const Model& m, const Buffers& b, const WeightSrc& w, const double* u_dev,
                       hipStream_t s);
 hipError_t launch_gather(const Model& m, const Buffers& b, float* out, hipStream_t s);

@@ -1772,8 +1772,10 @@ __device__ __forceinline__ double block_scan_add(double v) {
 // k_anc runs each segment whose slots span at most kCoopTiles tiles; a
 // heavier segment (concentrated weights) queues its tiles in chunks of
 // kChunkTiles for k_fill, whose waves each recompute the segment's runs and
-// write one chunk, so that heavy segments spread over many waves.
-// queued: called by k_fill for the tiles [tile_lo, tile_hi) of the segment.
+// write one chunk, so that heavy segments spread over many waves. (k_anc_all
+// has helper waves in the same launch find the heavy segments themselves.)
+// HEAVY: what a heavy segment's own wave does, queue it or leave it to them.
+// queued: called for the tiles [tile_lo, tile_hi) of a heavy segment.
 // One segment's loads, raw: its lanes' weights and its block records. Every
 // lane loads (indices clamped into the arrays, values masked at use), so no
 // load sits in a divergent branch that would consume it at once.
@@ -1840,7 +1842,9 @@ struct ResIn {
   double delta, u;
 };
 
-template <bool LOG>
+enum Heavy { kQueue, kLeave };
+
+template <bool LOG, Heavy HEAVY = kQueue>
 __device__ __forceinline__ void anc_segment(const Model& m, const Buffers& b, const ResIn& ci,
                                             int64_t seg, const SegIn& in, bool queued,
                                             int tile_lo, int tile_hi) {
@@ -1869,6 +1873,7 @@ __device__ __forceinline__ void anc_segment(const Model& m, const Buffers& b, co
   const int T0 = fs & ~3;  // tiles start on 16 bytes of anc
   const int ntiles = (fe - T0 + kSlotTile - 1) / kSlotTile;
   if (!queued && ntiles > kCoopTiles) {
+    if (HEAVY == kLeave) return;
     // a heavy segment: its tiles go to k_fill in chunks
     const int chunks = (ntiles + kChunkTiles - 1) / kChunkTiles;
     int base = 0;
@@ -2076,7 +2081,7 @@ __device__ __forceinline__ ResIn res_in(const Ctrl* c) {
 }
 
 // One wave per segment.
-template <bool LOG>
+template <bool LOG, Heavy HEAVY = kQueue>
 __device__ __forceinline__ void anc_seg(const Model& m, const Buffers& b, const WeightSrc& ws,
                                         int64_t seg) {
   const Ctrl* c = b.ctrl;
@@ -2084,7 +2089,78 @@ __device__ __forceinline__ void anc_seg(const Model& m, const Buffers& b, const 
   if (!ci.do_res || seg >= b.nseg) return;
   const bool second = ws.use_cur && c->cur;
   const SegIn in = load_seg(m, b, second ? ws.E1 : ws.E0, second ? ws.rec1 : ws.rec0, LOG, seg);
-  anc_segment<LOG>(m, b, ci, seg, in, false, 0, 0);
+  anc_segment<LOG, HEAVY>(m, b, ci, seg, in, false, 0, 0);
+}
+
+// Helper wave `id` of `count`: finds the heavy segments from the segments' slot
+// ranges (kHelpPerLane segments per lane, the bounds that anc_segment takes) and
+// writes the chunks id, id + count, ... of their tiles.
+template <bool LOG>
+__device__ __forceinline__ void anc_help(const Model& m, const Buffers& b, const WeightSrc& ws,
+                                         int id, int count) {
+  const Ctrl* c = b.ctrl;
+  const ResIn ci = res_in(c);
+  if (!ci.do_res) return;
+  const int lane = threadIdx.x, n = (int)m.n;
+  const int nseg = (int)b.nseg, per = (nseg + kWave - 1) / kWave;
+  const uint32_t cb = (uint32_t)(b.chunk >> 8);
+  const double nd = (double)m.n;
+  // the slots where the lane's segments, and the one after them, start
+  int at[kHelpPerLane + 1];
+#pragma unroll
+  for (int q = 0; q <= kHelpPerLane; ++q) {
+    at[q] = n;
+    if (q <= per) {  // uniform
+      const int seg = lane * per + q;
+      const int64_t blk = (int64_t)min(seg, nseg - 1) * kSegBlocks;
+      const double C = block_cdf(b.cpre[(uint32_t)(blk >> 8) / cb], b.pfx[blk]);
+      at[q] = seg == 0 ? 0 : seg >= nseg ? n : slot_bound(C, ci.u, nd, n);
+    }
+  }
+  int chunks[kHelpPerLane], tiles[kHelpPerLane];
+  int mine = 0;
+#pragma unroll
+  for (int q = 0; q < kHelpPerLane; ++q) {
+    tiles[q] = q < per && at[q + 1] > at[q]
+                   ? (at[q + 1] - (at[q] & ~3) + kSlotTile - 1) / kSlotTile
+                   : 0;
+    chunks[q] = tiles[q] > kCoopTiles ? (tiles[q] + kChunkTiles - 1) / kChunkTiles : 0;
+    mine += chunks[q];
+  }
+  const int incl = wave_scan(mine, lane, OpAdd());
+  const int total = readlane(incl, 63);
+  const bool second = ws.use_cur && c->cur;
+  for (int j = id; j < total; j += count) {  // uniform
+    const int owner = __popcll(__ballot(incl <= j));  // the first lane whose chunks reach past j
+    int first = readlane(incl - mine, owner), seg = 0, lo = 0, hi = 0;
+#pragma unroll
+    for (int q = 0; q < kHelpPerLane; ++q) {
+      const int k = readlane(chunks[q], owner);
+      if (j >= first && j < first + k) {
+        seg = owner * per + q;
+        lo = (j - first) * kChunkTiles;
+        hi = min(readlane(tiles[q], owner), lo + kChunkTiles);
+      }
+      first += k;
+    }
+    const SegIn in = load_seg(m, b, second ? ws.E1 : ws.E0, second ? ws.rec1 : ws.rec0, LOG, seg);
+    anc_segment<LOG, kLeave>(m, b, ci, seg, in, true, lo, hi);
+    __syncthreads();  // the next chunk clears the tile again
+  }
+}
+
+// The whole pass in one launch, for up to kWave kHelpPerLane segments: a wave
+// per segment, then helper waves for the heavy ones, which find them while the
+// others work. With no heavy segment (most steps) that takes no longer than the
+// segments themselves; k_fill's launch for an empty queue costs 2-4 us and a gap.
+// Beyond, a helper's look over all segments would outlast a launch.
+template <bool LOG>
+__global__ __launch_bounds__(kWave) void k_anc_all(Model m, Buffers b, WeightSrc ws) {
+  const int nseg = (int)b.nseg, j = (int)blockIdx.x;
+  if (j < nseg)
+    anc_seg<LOG, kLeave>(m, b, ws, j);
+  else
+    anc_help<LOG>(m, b, ws, j - nseg, (int)gridDim.x - nseg);
 }
 
 __global__ __launch_bounds__(kWave) void k_anc(Model m, Buffers b, WeightSrc ws) {
@@ -3608,14 +3684,18 @@ hipError_t launch_merge(const Model& m, const Buffers& b, int standalone, double
 }
 
 hipError_t launch_anc(const Model& m, const Buffers& b, const WeightSrc& w, hipStream_t s) {
-  if (w.log_src) return launch_k(k_anc_log, dim3((unsigned)b.nseg), dim3(kWave), s, m, b, w);
-  return launch_k(k_anc, dim3((unsigned)b.nseg), dim3(kWave), s, m, b, w);
-}
-
-hipError_t launch_fill(const Model& m, const Buffers& b, const WeightSrc& w, hipStream_t s) {
-  const unsigned grid = (unsigned)(b.hq_cap < kFillGrid ? b.hq_cap : kFillGrid);
-  if (w.log_src) return launch_k(k_fill_log, dim3(grid), dim3(kWave), s, m, b, w);
-  return launch_k(k_fill, dim3(grid), dim3(kWave), s, m, b, w);
+  if (b.nseg <= kWave * kHelpPerLane) {
+    const dim3 grid((unsigned)(b.nseg + (b.hq_cap < kHelpWaves ? b.hq_cap : kHelpWaves)));
+    if (w.log_src) return launch_k(k_anc_all<true>, grid, dim3(kWave), s, m, b, w);
+    return launch_k(k_anc_all<false>, grid, dim3(kWave), s, m, b, w);
+  }
+  const dim3 fill((unsigned)(b.hq_cap < kFillGrid ? b.hq_cap : kFillGrid));
+  const dim3 segs((unsigned)b.nseg);
+  hipError_t e = w.log_src ? launch_k(k_anc_log, segs, dim3(kWave), s, m, b, w)
+                           : launch_k(k_anc, segs, dim3(kWave), s, m, b, w);
+  if (e != hipSuccess) return e;
+  return w.log_src ? launch_k(k_fill_log, fill, dim3(kWave), s, m, b, w)
+                   : launch_k(k_fill, fill, dim3(kWave), s, m, b, w);
 }
 
 hipError_t launch_rna(const Model& m, const Buffers& b, const WeightSrc& w, const double* u_dev,
