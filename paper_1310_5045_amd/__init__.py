@@ -401,6 +401,12 @@ class Filter:
         return {buf[j].name.decode(): (buf[j].launches, buf[j].total_ms) for j in range(n.value)}
 
 
+# the same layout, for converting a batch's statistics column by column
+_STATS_DTYPE = np.dtype([(n, np.float64, (5,)) if n == "mean" else (n, np.dtype(t))
+                         for n, t in Stats._fields_])
+assert _STATS_DTYPE.itemsize == ctypes.sizeof(Stats)
+
+
 def _stats_dict(s: Stats) -> dict:
     return dict(k=s.k, resampled=bool(s.resampled), rolled_back=s.rolled_back, ess=s.ess,
                 max_logw=s.max_logw, log_sum=s.log_sum, delta=s.delta, cum=s.cum,
@@ -478,7 +484,12 @@ class Batch:
     def stats(self):
         buf = (Stats * self.count)()
         self._chk(lib().ppf_batch_stats(self.handle, buf, self.count))
-        return [_stats_dict(buf[j]) for j in range(self.count)]
+        a = np.frombuffer(buf, dtype=_STATS_DTYPE)
+        cols = [a[n].tolist() for n in ("k", "resampled", "rolled_back", "ess", "max_logw",
+                                        "log_sum", "delta", "cum")]
+        return [dict(k=k, resampled=bool(res), rolled_back=rb, ess=ess, max_logw=mx, log_sum=ls,
+                     delta=delta, cum=cum, mean=mean)
+                for k, res, rb, ess, mx, ls, delta, cum, mean in zip(*cols, a["mean"].copy())]
 
     def particles(self, track: int):
         n = self.n[track]

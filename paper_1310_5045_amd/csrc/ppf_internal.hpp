@@ -261,6 +261,9 @@ hipError_t launch_rna(const Model& m, const Buffers& b, const WeightSrc& w, cons
 hipError_t launch_gather(const Model& m, const Buffers& b, float* out, hipStream_t s);
 hipError_t launch_logw(const Model& m, const Buffers& b, hipStream_t s);
 hipError_t launch_set_mode(const Buffers& b, int32_t mode, hipStream_t s);
+// `count` control blocks to out (pinned host memory by its device address);
+// clear: and their roll-back reports zeroed.
+hipError_t launch_report(Ctrl* c, int32_t count, bool clear, Ctrl* out, hipStream_t s);
 hipError_t launch_records(const Model& m, const Buffers& b, const float* logw, hipStream_t s);
 hipError_t launch_philox(uint64_t seed, const uint32_t* ctr, uint32_t* out, int64_t n,
                          hipStream_t s);

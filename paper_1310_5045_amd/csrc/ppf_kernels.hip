@@ -23,6 +23,7 @@
 #include <cfloat>
 #include <climits>
 #include <cmath>
+#include <cstddef>
 #include <mutex>
 #include <tuple>
 #include <utility>
@@ -3245,6 +3246,21 @@ __global__ __launch_bounds__(256) void k_logw(Model m, Buffers b) {
 
 __global__ void k_set_mode(Ctrl* c, int32_t mode) { c->mode = mode; }
 
+// Control block blockIdx.x, eight bytes per thread, to pinned host memory; with
+// `clear` its roll-back report is zeroed (by the thread that has read it).
+static_assert(sizeof(Ctrl) % 8 == 0 && sizeof(Ctrl) / 8 <= kWave &&
+                  offsetof(Ctrl, rolled_back) % 8 == 4,
+              "one word per thread, the report in the upper half of one");
+__global__ __launch_bounds__(kWave) void k_report(Ctrl* c, int32_t clear, Ctrl* out) {
+  constexpr int kWords = (int)(sizeof(Ctrl) / 8);
+  const int t = threadIdx.x;
+  if (t >= kWords) return;
+  const uint64_t v = reinterpret_cast<const uint64_t*>(c + blockIdx.x)[t];
+  reinterpret_cast<uint64_t*>(out + blockIdx.x)[t] = v;
+  if (clear && t == (int)(offsetof(Ctrl, rolled_back) / 8) && (v >> 32) != 0)
+    c[blockIdx.x].rolled_back = 0;
+}
+
 __global__ __launch_bounds__(256) void k_philox(uint32_t k0, uint32_t k1,
                                                 const uint4* __restrict__ ctr,
                                                 uint4* __restrict__ out, int64_t n) {
@@ -3713,6 +3729,10 @@ hipError_t launch_logw(const Model& m, const Buffers& b, hipStream_t s) {
 
 hipError_t launch_set_mode(const Buffers& b, int32_t mode, hipStream_t s) {
   return launch_k(k_set_mode, dim3(1), dim3(1), s, b.ctrl, mode);
+}
+
+hipError_t launch_report(Ctrl* c, int32_t count, bool clear, Ctrl* out, hipStream_t s) {
+  return launch_k(k_report, dim3((unsigned)count), dim3(kWave), s, c, (int32_t)clear, out);
 }
 
 hipError_t launch_records(const Model& m, const Buffers& b, const float* logw, hipStream_t s) {
