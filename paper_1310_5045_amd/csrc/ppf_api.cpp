@@ -238,11 +238,10 @@ size_t carve(const ppf_params* p, char* base, Buffers* b, bool own_ctrl = true) 
     bb.asys = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * n));
     bb.rfirst = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * (Gr + 1)));
     bb.rdbase = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * Gr));
-    bb.rscum = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * (Gr + 1)));
-    bb.rns = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * 2));
+    bb.rscum = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * Gr));
     const int64_t nt = (2 * Gr + ppf::kSortTile - 1) / ppf::kSortTile;
     const int64_t nt2 = (Gr + ppf::kSortTile - 1) / ppf::kSortTile;
-    if (p->dlb == PPF_DLB_SGS) {
+    if (p->dlb == PPF_DLB_SGS && Gr > ppf::kRankGroups) {
       bb.rkey0 = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * 2 * Gr));
       bb.rkey1 = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * 2 * Gr));
       bb.rval0 = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * 2 * Gr));
@@ -250,8 +249,7 @@ size_t carve(const ppf_params* p, char* base, Buffers* b, bool own_ctrl = true) 
       bb.rhist = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * 256 * nt));
       bb.rrow = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * 256));
     }
-    bb.rtsum = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * 4 * nt2));
-    bb.rsidx = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * Gr));
+    bb.rtsum = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * 2 * nt2));
     bb.rstream = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * n));
   }
   if (p->init_kind == PPF_INIT_UNIFORM_ZORDER) {

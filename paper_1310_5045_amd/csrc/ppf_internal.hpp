@@ -69,6 +69,10 @@ constexpr int kFillGridBatch = 2048;  // waves of a batched fill, over all track
 constexpr int kFusedMaxP = 13;
 constexpr int kSortTile = 1024;      // pairs per tile of the list scans and of small sorts
 constexpr int64_t kSortLarge = 1 << 22;  // pairs from which the radix sort takes 4096-pair tiles
+// RPA: up to kRankGroups groups are ranked by counting; up to kRpaScanN
+// particles the groups' offspring ranges are found by a look at every slot.
+constexpr int kRankGroups = 8192;
+constexpr int64_t kRpaScanN = 1 << 22;
 // The allocation-free standalone resampler keeps its scratch in a device
 // array of this many bytes, one per device for the life of the process.
 constexpr size_t kStaticScratchBytes = size_t(4) << 20;
@@ -208,22 +212,20 @@ struct Buffers {
   int32_t* asys;     // RPA: ancestors of the global systematic resampling
   int64_t* rfirst;   // RPA: first systematic slot of each group's offspring (G + 1)
   int64_t* rdbase;   // RPA: per receiver group, its first surplus particle
-  int64_t* rscum;    // RPA: exclusive prefix of the senders' surplus (ns + 1)
-  int32_t* rns;      // RPA: number of senders
+  int64_t* rscum;    // RPA: per sender group, the surplus of the senders before it
   uint32_t* rkey0;   // RPA with SGS: radix-sort keys of the 2G list entries, ping
   uint32_t* rkey1;   //   and pong
   int32_t* rval0;    // RPA with SGS: their groups (after the sort: senders in order,
   int32_t* rval1;    //   then receivers in order), ping and pong
   uint32_t* rhist;   // RPA with SGS: digit counts per sort tile (256 x tiles)
   uint32_t* rrow;    // RPA with SGS: digit totals (256)
-  uint64_t* rtsum;   // RPA: per list tile, the sum of the values and the count present
+  uint64_t* rtsum;   // RPA: per list tile, the sum of the values
   uint32_t* zkey0;   // Z-ordered init: the particles' sort keys, ping
   uint32_t* zkey1;   //   and pong
   int32_t* zval0;    // Z-ordered init: their draw indices, ping (after the sort: the
   int32_t* zval1;    //   draw index at each position) and pong
   uint32_t* zhist;   // Z-ordered init: digit counts per sort tile
   uint32_t* zrow;    // Z-ordered init: digit totals
-  int32_t* rsidx;    // RPA: each sender group's position in the sender order (G)
   int32_t* rstream;  // RPA: the senders' surplus offspring in schedule order (N)
   int32_t* aloc;     // ARNA: each group's local resampling (n global indices)
   double* Wg;        // ARNA: each group's share of the normalised weight

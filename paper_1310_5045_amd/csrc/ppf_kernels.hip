@@ -2476,7 +2476,7 @@ __global__ __launch_bounds__(256) void k_arna_exchange(Model m, Buffers b) {
 // free slots of the receivers (N_g < n). Greedy matching is the overlap of
 // the senders' surplus intervals and the receivers' deficit intervals laid
 // end to end in schedule order (group order for GS, by size descending for
-// SGS), so each routed slot finds its sender by binary search.
+// SGS): a routed particle is named by its place in that stream.
 
 // First index of the non-decreasing a[0..n) with a[i] >= v.
 __device__ __forceinline__ int64_t lower_bound_i32(const int32_t* a, int64_t n, int64_t v) {
@@ -2493,13 +2493,112 @@ __device__ __forceinline__ int64_t rpa_count(const Buffers& b, int64_t g) {
   return b.rfirst[g + 1] - b.rfirst[g];
 }
 
-// The groups' offspring ranges: one binary search per group boundary.
+// The groups' offspring ranges, by a look at every slot: where the ancestors'
+// group changes, the groups after the last slot's up to this one start here. One
+// pass over 4 N bytes; a search per group is a chain of log2 N loads, 10 us for
+// 4096 groups of 2^20 particles against 4.7 us, and the better one once N
+// outgrows the caches (38 M: 19 us, against 30 us for the bytes alone).
+__global__ __launch_bounds__(256) void k_rpa_bounds(Model m, Buffers b) {
+  const Ctrl* c = b.ctrl;
+  if (!c->do_resample) return;
+  const int64_t N = m.n;
+  const int64_t t0 = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
+  const uint32_t n = (uint32_t)m.rpa_group;
+  const int lane = threadIdx.x & 63;
+  int prev = t0 > 0 ? (int)((uint32_t)b.asys[min(t0, N) - 1] / n) : -1;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    // past the last slot: a boundary to "group G", once
+    const int64_t t = min(t0 + i, N);
+    const int g = t < N ? (int)((uint32_t)b.asys[t] / n) : m.rpa_G;
+    if (g > prev && t0 + i <= N) b.rfirst[g] = t;
+    // the empty groups between are written by the whole wave
+    uint64_t gaps = __ballot(g > prev + 1 && t0 + i <= N);
+    while (gaps) {  // uniform
+      const int l = __builtin_ctzll(gaps);
+      gaps &= gaps - 1;
+      const int g0 = readlane(prev, l) + 1, g1 = readlane(g, l);
+      const int64_t first = (int64_t)readlane((uint64_t)t, l);
+      for (int x = g0 + lane; x < g1; x += 64) b.rfirst[x] = first;
+    }
+    prev = g;
+  }
+}
+
+// The same by one binary search per group boundary.
 __global__ __launch_bounds__(256) void k_rpa_first(Model m, Buffers b) {
   const Ctrl* c = b.ctrl;
   if (!c->do_resample) return;
   const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t N = m.n, G = m.rpa_G;
   if (g <= G) b.rfirst[g] = g == G ? N : lower_bound_i32(b.asys, N, g * (int64_t)m.rpa_group);
+}
+
+// The whole plan for up to kRankGroups groups: group g's base in the stream is
+// the sum of the values before it in its side's order, taken over all groups by
+// 16 lanes (the values in LDS). G^2 compares: 10.6 us for 4096 groups, where the
+// radix sort and the scans of the lists were 16 launches and 80 us; the compares
+// would overtake them between 8192 and 16,384 groups.
+template <bool SORTED>
+__global__ __launch_bounds__(256) void k_rpa_rank(Model m, Buffers b) {
+  const Ctrl* c = b.ctrl;
+  if (!c->do_resample) return;
+  // the groups' first slots (below 2^31), then their offspring less their
+  // slots, 0 past the groups
+  __shared__ __align__(16) int v[kRankGroups + 4];
+  const int G = m.rpa_G, n = m.rpa_group, t = threadIdx.x, r = t & 15;
+  const int* first = reinterpret_cast<const int*>(b.rfirst);  // their low words
+  for (int j0 = t; j0 <= G; j0 += 2048) {  // eight loads at a time
+    int x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = first[2 * min(j0 + 256 * u, G)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (j0 + 256 * u <= G) v[j0 + 256 * u] = x[u];
+  }
+  __syncthreads();
+  // the differences, 1024 groups at a time from below (each round reads what
+  // later rounds have not written yet), zeros up to a multiple of 64 groups
+  const int G64 = (G + 63) & ~63;
+  for (int j0 = 0; j0 < G64; j0 += 1024) {
+    const int j = j0 + 4 * t;
+    int f[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) f[i] = v[min(j + i, G)];
+    __syncthreads();
+    if (j < G64) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[j + i] = j + i < G ? f[i + 1] - f[i] - n : 0;
+    }
+    __syncthreads();
+  }
+  const int g = min((int)blockIdx.x * 16 + (t >> 4), G - 1);
+  const int vg = v[g], neg = vg > 0 ? 0 : -1;
+  const int wg = (vg ^ neg) - neg;  // the group's surplus or deficit
+  // GS: before g when the group is; SGS: when its value is larger, or equal and
+  // the group is. (Values of the other side, and past the groups, are not
+  // positive here.)
+  int pre = 0;
+#pragma unroll 4
+  for (int j = 4 * r; j < G; j += 64) {
+    const int4 q = *reinterpret_cast<const int4*>(v + j);
+    const int w4[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int w = (w4[i] ^ neg) - neg, lower = j + i < g ? 1 : 0;
+      if (SORTED)
+        pre += w & -(int)(w + lower > wg);
+      else
+        pre += max(w, 0) & -lower;
+    }
+  }
+  pre = row_allreduce(pre, OpAdd());
+  if (r == 0 && (int)blockIdx.x * 16 + (t >> 4) < G && wg > 0) {
+    if (vg > 0)
+      b.rscum[g] = pre;
+    else
+      b.rdbase[g] = pre;
+  }
 }
 
 // Surplus (side 0) or deficit (side 1) of group g; 0 when it is not a
@@ -2736,12 +2835,11 @@ __device__ __forceinline__ int64_t rpa_at(const Model& m, const Buffers& b, int 
 }
 
 // The plan: over each side's list in schedule order, the exclusive prefix of
-// the values (and, for the senders, of their count), in three launches:
-// per tile of kSortTile positions the sum and the count present
+// the values, in three launches: per tile of kSortTile positions the sum
 // (k_rpa_plan_tiles), their exclusive prefixes over the tiles
-// (k_rpa_plan_scan, one workgroup per side), then each position's prefixes
-// (k_rpa_plan_apply): each sender's position in the sender order and the
-// prefix of the surplus before it, each receiver's first surplus particle.
+// (k_rpa_plan_scan, one workgroup per side), then each position's prefix
+// (k_rpa_plan_apply): the surplus before each sender, each receiver's first
+// surplus particle.
 __global__ __launch_bounds__(256) void k_rpa_plan_tiles(Model m, Buffers b) {
   __shared__ uint64_t sh[4];
   const Ctrl* c = b.ctrl;
@@ -2750,22 +2848,14 @@ __global__ __launch_bounds__(256) void k_rpa_plan_tiles(Model m, Buffers b) {
   const int64_t G = m.rpa_G, n = m.rpa_group;
   const int64_t nt2 = (G + kSortTile - 1) / kSortTile;
   const int64_t k0 = (int64_t)blockIdx.x * kSortTile + 4 * threadIdx.x;
-  uint64_t sv = 0, sp = 0;
+  uint64_t sv = 0;
   for (int i = 0; i < 4; ++i) {
     const int64_t k = k0 + i;
-    if (k < G) {
-      const uint64_t v = rpa_value(b, n, rpa_at(m, b, side, k), side);
-      sv += v;
-      sp += v > 0 ? 1 : 0;
-    }
+    if (k < G) sv += rpa_value(b, n, rpa_at(m, b, side, k), side);
   }
-  uint64_t tv, tp;
+  uint64_t tv;
   block_excl_sum(sv, sh, &tv);
-  block_excl_sum(sp, sh, &tp);
-  if (threadIdx.x == 0) {
-    b.rtsum[2 * (side * nt2 + blockIdx.x)] = tv;
-    b.rtsum[2 * (side * nt2 + blockIdx.x) + 1] = tp;
-  }
+  if (threadIdx.x == 0) b.rtsum[side * nt2 + blockIdx.x] = tv;
 }
 
 __global__ __launch_bounds__(256) void k_rpa_plan_scan(Model m, Buffers b) {
@@ -2775,24 +2865,15 @@ __global__ __launch_bounds__(256) void k_rpa_plan_scan(Model m, Buffers b) {
   const int side = blockIdx.x;
   const int64_t G = m.rpa_G;
   const int64_t nt2 = (G + kSortTile - 1) / kSortTile;
-  uint64_t* ts = b.rtsum + 2 * side * nt2;
-  uint64_t cv = 0, cp = 0;
+  uint64_t* ts = b.rtsum + side * nt2;
+  uint64_t cv = 0;
   for (int64_t i0 = 0; i0 < nt2; i0 += 256) {
     const int64_t i = i0 + threadIdx.x;
-    const uint64_t v = i < nt2 ? ts[2 * i] : 0, p = i < nt2 ? ts[2 * i + 1] : 0;
-    uint64_t tv, tp;
+    const uint64_t v = i < nt2 ? ts[i] : 0;
+    uint64_t tv;
     const uint64_t ev = block_excl_sum(v, sh, &tv);
-    const uint64_t ep = block_excl_sum(p, sh, &tp);
-    if (i < nt2) {
-      ts[2 * i] = cv + ev;
-      ts[2 * i + 1] = cp + ep;
-    }
+    if (i < nt2) ts[i] = cv + ev;
     cv += tv;
-    cp += tp;
-  }
-  if (side == 0 && threadIdx.x == 0) {
-    b.rns[0] = (int32_t)cp;
-    b.rscum[cp] = (int64_t)cv;
   }
 }
 
@@ -2806,34 +2887,29 @@ __global__ __launch_bounds__(256) void k_rpa_plan_apply(Model m, Buffers b) {
   const int64_t k0 = (int64_t)blockIdx.x * kSortTile + 4 * threadIdx.x;
   int64_t g[4];
   uint64_t v[4];
-  uint64_t sv = 0, sp = 0;
+  uint64_t sv = 0;
   for (int i = 0; i < 4; ++i) {
     const int64_t k = k0 + i;
     g[i] = k < G ? rpa_at(m, b, side, k) : 0;
     v[i] = k < G ? rpa_value(b, n, g[i], side) : 0;
     sv += v[i];
-    sp += v[i] > 0 ? 1 : 0;
   }
-  uint64_t tv, tp;
-  uint64_t pv = block_excl_sum(sv, sh, &tv) + b.rtsum[2 * (side * nt2 + blockIdx.x)];
-  uint64_t pp = block_excl_sum(sp, sh, &tp) + b.rtsum[2 * (side * nt2 + blockIdx.x) + 1];
+  uint64_t tv;
+  uint64_t pv = block_excl_sum(sv, sh, &tv) + b.rtsum[side * nt2 + blockIdx.x];
   for (int i = 0; i < 4; ++i) {
     if (v[i] > 0) {
-      if (side == 0) {
-        b.rscum[pp] = (int64_t)pv;
-        b.rsidx[g[i]] = (int32_t)pp;
-      } else {
+      if (side == 0)
+        b.rscum[g[i]] = (int64_t)pv;
+      else
         b.rdbase[g[i]] = (int64_t)pv;
-      }
       pv += v[i];
-      pp += 1;
     }
   }
 }
 
 // The surplus stream: the q-th surplus offspring in schedule order is
-// offspring n + j of the sender at position i of the sender order, where q =
-// (surplus of the senders before i) + j. Each thread takes four consecutive
+// offspring n + j of the sender g with q = (surplus of the senders before g) +
+// j. Each thread takes four consecutive
 // systematic slots t: slot t is offspring t - first(g) of the group g that
 // holds its ancestor (every load is issued before any store).
 __global__ __launch_bounds__(256) void k_rpa_stream(Model m, Buffers b) {
@@ -2861,7 +2937,7 @@ __global__ __launch_bounds__(256) void k_rpa_stream(Model m, Buffers b) {
     // ancestors are below N < 2^31: a 32-bit quotient
     const int64_t g = (int64_t)((uint32_t)a[i] / (uint32_t)n);
     const int64_t j = t0 + i - b.rfirst[g] - n;
-    q[i] = (t0 + i < N && j >= 0) ? b.rscum[b.rsidx[g]] + j : -1;  // -1: kept by its group
+    q[i] = (t0 + i < N && j >= 0) ? b.rscum[g] + j : -1;  // -1: kept by its group
   }
   int32_t* __restrict__ out = b.rstream;
 #pragma unroll
@@ -3576,17 +3652,26 @@ hipError_t launch_arna(const Model& m, const Buffers& b, hipStream_t s) {
 
 hipError_t launch_rpa(const Model& m, const Buffers& b, hipStream_t s) {
   const int64_t G = m.rpa_G;
-  hipError_t e = launch_k(k_rpa_first, dim3(grid_for(G + 1, 256)), dim3(256), s, m, b);
-  if (e == hipSuccess && m.dlb == 1) {
-    const int64_t cnt = 2 * G;
-    e = launch_k(k_rpa_keys, dim3(grid_for(cnt, 256)), dim3(256), s, m, b);
+  // (N + 1 entries: the last slot's successor closes the last group)
+  hipError_t e = m.n <= kRpaScanN
+                     ? launch_k(k_rpa_bounds, dim3(grid_for(m.n / 4 + 1, 256)), dim3(256), s, m, b)
+                     : launch_k(k_rpa_first, dim3(grid_for(G + 1, 256)), dim3(256), s, m, b);
+  if (G <= kRankGroups) {
     if (e == hipSuccess)
-      e = radix_sort(b.rkey0, b.rkey1, b.rval0, b.rval1, b.rhist, b.rrow, cnt, false, b.ctrl, s);
+      e = launch_k(m.dlb == 1 ? k_rpa_rank<true> : k_rpa_rank<false>, dim3(grid_for(G, 16)),
+                   dim3(256), s, m, b);
+  } else {
+    if (e == hipSuccess && m.dlb == 1) {
+      const int64_t cnt = 2 * G;
+      e = launch_k(k_rpa_keys, dim3(grid_for(cnt, 256)), dim3(256), s, m, b);
+      if (e == hipSuccess)
+        e = radix_sort(b.rkey0, b.rkey1, b.rval0, b.rval1, b.rhist, b.rrow, cnt, false, b.ctrl, s);
+    }
+    const unsigned nt2 = (unsigned)((G + kSortTile - 1) / kSortTile);
+    if (e == hipSuccess) e = launch_k(k_rpa_plan_tiles, dim3(nt2, 2), dim3(256), s, m, b);
+    if (e == hipSuccess) e = launch_k(k_rpa_plan_scan, dim3(2), dim3(256), s, m, b);
+    if (e == hipSuccess) e = launch_k(k_rpa_plan_apply, dim3(nt2, 2), dim3(256), s, m, b);
   }
-  const unsigned nt2 = (unsigned)((G + kSortTile - 1) / kSortTile);
-  if (e == hipSuccess) e = launch_k(k_rpa_plan_tiles, dim3(nt2, 2), dim3(256), s, m, b);
-  if (e == hipSuccess) e = launch_k(k_rpa_plan_scan, dim3(2), dim3(256), s, m, b);
-  if (e == hipSuccess) e = launch_k(k_rpa_plan_apply, dim3(nt2, 2), dim3(256), s, m, b);
   const int64_t quads = (m.n + 3) / 4;
   if (e == hipSuccess) e = launch_k(k_rpa_stream, dim3(grid_for(quads, 256)), dim3(256), s, m, b);
   if (e == hipSuccess) e = launch_k(k_rpa_route, dim3(grid_for(quads, 256)), dim3(256), s, m, b);
