@@ -14,9 +14,8 @@
 //                  segment's CDF
 //   k_fill         the slots of heavy segments queued by k_anc (concentrated
 //                  weights), in chunks of tiles
-//   (or k_rna_local + k_rna_exchange: RNA of Section 3, one workgroup per
-//                  group of particles; k_arna_* for ARNA; k_rpa_* after k_fill
-//                  for RPA)
+//   (or k_rna: RNA of Section 3, one wave or workgroup per group of particles;
+//                  k_arna_* for ARNA; k_rpa_* after the ancestors for RPA)
 #include "ppf_internal.hpp"
 
 #include <array>
@@ -2207,126 +2206,169 @@ __global__ __launch_bounds__(kWave) void k_fill_log(Model m, Buffers b, WeightSr
 }
 
 // ------------------------------------------------------------------- RNA
-__device__ __forceinline__ double wave_sum_d(double v, int lane) {
-  return wave_reduce(v, lane, OpAdd());
+// Orders the LDS accesses of one wave's lanes (they are served in order; this
+// keeps the compiler from moving them).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// One workgroup per group g (Section 3): local systematic resampling of the
-// group's normalised weights, slot weight W_g / n, and the last `moved` slots
-// taken from group g-1's local resampling (recomputed here, so no workgroup
-// waits for another).
-// The normalised weights of group gg's ng particles (E relative to its
-// block maximum, or absolute fp32 log weights), their sum W (returned) and
-// their local CDF in 2^60 fixed point, C[0..ng), by one 256-thread
-// workgroup; dsum and wsum are 4 entries of LDS scratch each.
-__device__ __forceinline__ double group_cdf(const WeightSrc& ws, const float* E, const double* rec,
-                                            double lognorm, int64_t gg, int ng, uint64_t* C,
-                                            double* dsum, uint64_t* wsum) {
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int ipt = (ng + 255) / 256;
-  const int64_t base = gg * ng;
+// A group's resampling (Section 3) by WAVES waves, four consecutive particles
+// and slots per lane: one wave for groups up to kWaveGroup particles, so that no
+// barrier waits, a block's factor is one exp for four particles and the scans
+// are a quarter; four waves for larger groups. The kernel is bound by issue
+// (divisions, exps, searches): 4096 groups of 256 took 13.2 us with one particle
+// per lane and a search per slot, 300 groups of 1000 10.3 us with loads that
+// waited for each other.
+constexpr int kWaveGroup = 256;
+template <int WAVES>
+struct GroupLds {
+  static constexpr int kTeams = 4 / WAVES;  // groups per workgroup
+  __align__(16) uint64_t C[kTeams][256 * WAVES];  // a group's local CDF, 2^60 fixed point
+  double dsum[4];
+  uint64_t wsum[4];
+};
+
+// The share W of group gg's ng particles (E relative to its block maximum, or
+// absolute fp32 log weights) and, by local systematic resampling with the
+// uniform u, the particles a[0..3] (indices in the group) of this lane's slots 4
+// tl + i: the first j with C_j > (l + u) / ng (the identity when the group has
+// no weight). team: the group's place in the workgroup; tl: thread in the group.
+template <int WAVES>
+__device__ __forceinline__ double group_resample(const WeightSrc& ws, const float* E,
+                                                 const double* rec, double lognorm, int64_t gg,
+                                                 int ng, double inv_ng, double u,
+                                                 GroupLds<WAVES>& L, int team, int tl,
+                                                 int (&a)[4]) {
+  const int lane = threadIdx.x & 63, w = wave_index();
+  uint64_t* const C = L.C[team];
+  const int64_t base = gg * ng, idx = base + 4 * tl;
+  const int64_t last = base + ng - 1;
+  const int here = max(0, min(4, ng - 4 * tl));  // this lane's particles
+  float x[4];
+  if (here == 4 && (reinterpret_cast<uintptr_t>(E + idx) & 15) == 0) {
+    const float4 v = *reinterpret_cast<const float4*>(E + idx);
+    x[0] = v.x;
+    x[1] = v.y;
+    x[2] = v.z;
+    x[3] = v.w;
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = E[min(idx + j, last)];
+  }
   double wl[4];
-  double part = 0.0;
-  for (int j = 0; j < ipt; ++j) {
-    const int li = t * ipt + j;
-    wl[j] = 0.0;
-    if (li < ng) {
-      const int64_t idx = base + li;
-      if (ws.log_src) {
-        wl[j] = exp((double)E[idx] - lognorm);
-      } else {
-        const double mb = rec[(idx / kBlock) * kRec];
-        wl[j] = mb == -INFINITY ? 0.0 : (double)E[idx] * exp(mb - lognorm);
-      }
-      part += wl[j];
+  if (ws.log_src) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) wl[j] = j < here ? exp((double)x[j] - lognorm) : 0.0;
+  } else {
+    // the four lie in one block of records, or in two
+    const int64_t b0 = min(idx, last) / kBlock, b3 = min(idx + 3, last) / kBlock;
+    const double m0 = rec[b0 * kRec], m3 = rec[b3 * kRec];
+    const double f0 = exp(m0 - lognorm);
+    double f3 = f0;
+    if (__ballot(b0 != b3)) f3 = exp(m3 - lognorm);  // uniform
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool second = min(idx + j, last) / kBlock != b0;
+      const double mb = second ? m3 : m0, f = second ? f3 : f0;
+      wl[j] = j >= here || mb == -INFINITY ? 0.0 : (double)x[j] * f;
     }
   }
-  part = wave_sum_d(part, lane);
-  if (lane == 0) dsum[w] = part;
-  __syncthreads();
-  const double W = (dsum[0] + dsum[1]) + (dsum[2] + dsum[3]);
-  __syncthreads();
-  uint64_t run = 0, v[4];
-  for (int j = 0; j < ipt; ++j) {
-    const uint64_t wf = (W > 0.0) ? __double2ull_rn(wl[j] / W * 0x1p60) : 0ull;
-    run += wf;
+  double W = wave_reduce(((wl[0] + wl[1]) + wl[2]) + wl[3], lane, OpAdd());
+  if (WAVES > 1) {
+    if (lane == 0) L.dsum[w] = W;
+    __syncthreads();
+    W = (L.dsum[0] + L.dsum[1]) + (L.dsum[2] + L.dsum[3]);
+  }
+  uint64_t v[4], run = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    run += (W > 0.0) ? __double2ull_rn(wl[j] / W * 0x1p60) : 0ull;
     v[j] = run;
   }
-  const uint64_t incl = wave_scan(run, lane, OpAdd());
-  if (lane == 63) wsum[w] = incl;
-  __syncthreads();
-  uint64_t before = 0;
-  for (int j = 0; j < w; ++j) before += wsum[j];
-  for (int j = 0; j < ipt; ++j) {
-    const int li = t * ipt + j;
-    if (li < ng) C[li] = before + incl - run + v[j];
+  uint64_t before = wave_scan(run, lane, OpAdd()) - run;
+  if (WAVES > 1) {
+    if (lane == 63) L.wsum[w] = before + run;
+    __syncthreads();
+    for (int j = 0; j < w; ++j) before += L.wsum[j];
   }
-  __syncthreads();
+  // (entries from ng on repeat the total; no search reads them)
+#pragma unroll
+  for (int j = 0; j < 4; ++j) C[4 * tl + j] = before + v[j];
+  if (WAVES > 1)
+    __syncthreads();
+  else
+    wave_sync();
+  // the first slot by binary search, the others from their predecessor's: the
+  // same particle, the next, or a search beyond
+  int lo = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int l = 4 * tl + i;
+    const uint64_t us = (uint64_t)(((double)min(l, ng - 1) + u) * inv_ng * 0x1p60);
+    int hi = ng - 1;
+    if (i > 0) {
+      if (lo < hi && !(C[lo] > us)) ++lo;
+      if (lo >= hi || C[lo] > us) hi = lo;
+    }
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (C[mid] > us)
+        hi = mid;
+      else
+        lo = mid + 1;
+    }
+    a[i] = W > 0.0 ? lo : l;
+  }
   return W;
 }
 
-// Local systematic resampling of slot l of a group with CDF C (ng entries)
-// and uniform u: the first j with C_j > (l + u) / ng in 2^60 fixed point (the
-// identity when the group has no weight).
-__device__ __forceinline__ int local_slot(const uint64_t* C, int ng, double inv_ng, double W,
-                                          double u, int l) {
-  if (!(W > 0.0)) return l;
-  const uint64_t us = (uint64_t)(((double)l + u) * inv_ng * 0x1p60);
-  int lo = 0, hi = ng - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (C[mid] > us)
-      hi = mid;
-    else
-      lo = mid + 1;
-  }
-  return lo;
-}
-
-// One workgroup per group g (Section 3): local systematic resampling of the
-// group's normalised weights, slot weight W_g / n, and the last `moved` slots
-// taken from group g-1's local resampling (recomputed here, so no workgroup
-// waits for another).
+// RNA of one group: its local resampling, the last `moved` slots of which go to
+// the same slots of group g+1 on the ring (so group g's come from g-1, and no
+// workgroup needs another's result), and its slot weight W_g / n.
+template <int WAVES>
 __device__ __forceinline__ void rna_body(const Model& m, const Buffers& b, const WeightSrc& ws,
-                                         const double* __restrict__ u_dev, int64_t g) {
-  __shared__ uint64_t C[2][kMaxGroup];
-  __shared__ double dsum[4];
-  __shared__ uint64_t wsum[4];
-  Ctrl* c = b.ctrl;
+                                         const double* __restrict__ u_dev, int64_t block) {
+  __shared__ GroupLds<WAVES> L;
+  const Ctrl* c = b.ctrl;
   if (!c->do_resample) return;
-  const bool second = ws.use_cur && c->cur;
-  const float* E = second ? ws.E1 : ws.E0;
-  const double* rec = second ? ws.rec1 : ws.rec0;
-  const int ng = m.group;
+  const int team = WAVES == 1 ? wave_index() : 0;
+  const int64_t g = block * (4 / WAVES) + team;
   const int64_t G = m.G;
-  const int64_t prev = (g + G - 1) % G;
-  const double lognorm = c->delta;
-  const int t = threadIdx.x;
-  double Wg[2];
-  double ug[2];
-  for (int side = 0; side < 2; ++side) {
-    const int64_t gg = side ? prev : g;
-    Wg[side] = group_cdf(ws, E, rec, lognorm, gg, ng, C[side], dsum, wsum);
-    if (u_dev) {
-      ug[side] = u_dev[gg];
-    } else {
-      const uint4 rr = draw(m, (uint32_t)gg, (uint32_t)c->k, kRna, 0u);
-      ug[side] = u53(rr.x, rr.y);
-    }
+  if (g >= G) return;  // whole waves, of groups of one wave (no barriers)
+  const int tl = (int)threadIdx.x - (WAVES == 1 ? 64 * team : 0);
+  const bool second = ws.use_cur && c->cur;
+  const int ng = m.group;
+  double u;
+  if (u_dev) {
+    u = u_dev[g];
+  } else {
+    const uint4 rr = draw(m, (uint32_t)g, (uint32_t)c->k, kRna, 0u);
+    u = u53(rr.x, rr.y);
   }
-  // slots of group g: own local resampling, then the received tail
-  for (int l = t; l < ng; l += 256) {
-    const int side = (l >= ng - m.moved) ? 1 : 0;
-    const int64_t gg = side ? prev : g;
-    const int j = local_slot(C[side], ng, m.inv_group, Wg[side], ug[side], l);
-    b.anc[g * ng + l] = (int32_t)(gg * ng + j);
+  int a[4];
+  const double W = group_resample<WAVES>(ws, second ? ws.E1 : ws.E0, second ? ws.rec1 : ws.rec0,
+                                         c->delta, g, ng, m.inv_group, u, L, team, tl, a);
+  const int64_t mine = g * ng, next = (g + 1 == G ? 0 : g + 1) * (int64_t)ng;
+  const int stay = ng - m.moved;  // slots from here on go to the next group
+  const int l = 4 * tl;
+  int32_t* out = b.anc + (l < stay ? mine : next) + l;
+  if (l + 4 <= ng && (l + 4 <= stay || l >= stay) &&
+      (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+    const int p = (int)mine;
+    *reinterpret_cast<int4*>(out) = make_int4(p + a[0], p + a[1], p + a[2], p + a[3]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (l + i < ng) b.anc[(l + i < stay ? mine : next) + l + i] = (int32_t)(mine + a[i]);
   }
-  if (t == 0) b.lwg[g] = log(Wg[0] / (double)ng);
+  if (tl == 0) b.lwg[g] = log(W / (double)ng);
 }
 
+template <int WAVES>
 __global__ __launch_bounds__(256) void k_rna(Model m, Buffers b, WeightSrc ws,
                                              const double* __restrict__ u_dev) {
-  rna_body(m, b, ws, u_dev, blockIdx.x);
+  rna_body<WAVES>(m, b, ws, u_dev, blockIdx.x);
 }
 
 // ------------------------------------------------------------------ ARNA
@@ -2387,30 +2429,30 @@ __device__ int64_t ring_pred(const Model& m, uint32_t key, int64_t G, int64_t g)
   return (int64_t)y;
 }
 
-// One workgroup per group: W_g, the local systematic resampling (global
-// indices into aloc), and the tracking count.
-// The local resampling of group g into aloc and its share W_g (RNA and
-// ARNA; ARNA also counts the tracking groups).
-template <bool ARNA>
-__device__ __forceinline__ void group_local_body(const Model& m, const Buffers& b, int64_t g) {
-  __shared__ uint64_t C[kMaxGroup];
-  __shared__ double dsum[4];
-  __shared__ uint64_t wsum[4];
+// W_g, the local systematic resampling (global indices into aloc), and the
+// tracking count.
+template <int WAVES>
+__device__ __forceinline__ void arna_local_body(const Model& m, const Buffers& b, int64_t block) {
+  __shared__ GroupLds<WAVES> L;
   Ctrl* c = b.ctrl;
   if (!c->do_resample) return;
+  const int team = WAVES == 1 ? wave_index() : 0;
+  const int64_t g = block * (4 / WAVES) + team;
+  if (g >= m.G) return;
+  const int tl = (int)threadIdx.x - (WAVES == 1 ? 64 * team : 0);
   const int cur = c->cur;
   const WeightSrc ws{b.E0, b.E1, b.R0, b.R1, 1, 0};
-  const float* E = cur ? b.E1 : b.E0;
-  const double* rec = cur ? b.R1 : b.R0;
   const int ng = m.group;
-  const double W = group_cdf(ws, E, rec, c->delta, g, ng, C, dsum, wsum);
   const uint4 rr = draw(m, (uint32_t)g, (uint32_t)c->k, kRna, 0u);
-  const double u = u53(rr.x, rr.y);
-  for (int l = threadIdx.x; l < ng; l += 256)
-    b.aloc[g * ng + l] = (int32_t)(g * ng + local_slot(C, ng, m.inv_group, W, u, l));
-  if (threadIdx.x == 0) {
+  int a[4];
+  const double W = group_resample<WAVES>(ws, cur ? b.E1 : b.E0, cur ? b.R1 : b.R0, c->delta, g, ng,
+                                         m.inv_group, u53(rr.x, rr.y), L, team, tl, a);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (4 * tl + i < ng) b.aloc[g * ng + 4 * tl + i] = (int32_t)(g * ng + a[i]);
+  if (tl == 0) {
     b.Wg[g] = W;
-    if (ARNA && W >= m.arna_share) atomicAdd(&c->arna_tracking, 1);
+    if (W >= m.arna_share) atomicAdd(&c->arna_tracking, 1);
   }
 }
 
@@ -2437,29 +2479,9 @@ __device__ __forceinline__ void arna_exchange_body(const Model& m, const Buffers
   }
 }
 
+template <int WAVES>
 __global__ __launch_bounds__(256) void k_arna_local(Model m, Buffers b) {
-  group_local_body<true>(m, b, blockIdx.x);
-}
-
-// RNA (Section 3) in two launches: the groups' local resampling
-// (k_rna_local), then each group's last `moved` slots from group g-1's
-// (k_rna_exchange); the same ancestors and weights as rna_body, which
-// recomputes group g-1's local resampling in every workgroup instead.
-__global__ __launch_bounds__(256) void k_rna_local(Model m, Buffers b) {
-  group_local_body<false>(m, b, blockIdx.x);
-}
-
-__global__ __launch_bounds__(256) void k_rna_exchange(Model m, Buffers b) {
-  const Ctrl* c = b.ctrl;
-  if (!c->do_resample) return;
-  const int64_t g = blockIdx.x, G = m.G;
-  const int ng = m.group;
-  const int64_t prev = (g + G - 1) % G;
-  for (int l = threadIdx.x; l < ng; l += 256) {
-    const int64_t src = (l >= ng - m.moved) ? prev : g;
-    b.anc[g * ng + l] = b.aloc[src * ng + l];
-  }
-  if (threadIdx.x == 0) b.lwg[g] = log(b.Wg[g] / (double)ng);
+  arna_local_body<WAVES>(m, b, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_arna_exchange(Model m, Buffers b) {
@@ -3289,7 +3311,8 @@ __global__ __launch_bounds__(256) void k_rna_batch(const Model* __restrict__ ms,
                                                    const BatchItem* __restrict__ items) {
   const BatchItem it = items[blockIdx.x];
   const Buffers& b = bs[it.track];
-  rna_body(ms[it.track], b, own_weights(b), nullptr, it.idx);
+  // (a work item per group, whatever its size: one group to a workgroup)
+  rna_body<4>(ms[it.track], b, own_weights(b), nullptr, it.idx);
 }
 
 // ------------------------------------------------------------- utilities
@@ -3638,14 +3661,11 @@ hipError_t launch_rna_batch(const Model* ms, const Buffers* bs, const BatchItem*
   return launch_k(k_rna_batch, dim3((unsigned)n_items), dim3(256), s, ms, bs, items);
 }
 
-hipError_t launch_rna_groups(const Model& m, const Buffers& b, hipStream_t s) {
-  const hipError_t e = launch_k(k_rna_local, dim3((unsigned)m.G), dim3(256), s, m, b);
-  if (e != hipSuccess) return e;
-  return launch_k(k_rna_exchange, dim3((unsigned)m.G), dim3(256), s, m, b);
-}
-
 hipError_t launch_arna(const Model& m, const Buffers& b, hipStream_t s) {
-  const hipError_t e = launch_k(k_arna_local, dim3((unsigned)m.G), dim3(256), s, m, b);
+  const hipError_t e =
+      m.group <= kWaveGroup
+          ? launch_k(k_arna_local<1>, dim3(grid_for(m.G, 4)), dim3(256), s, m, b)
+          : launch_k(k_arna_local<4>, dim3((unsigned)m.G), dim3(256), s, m, b);
   if (e != hipSuccess) return e;
   return launch_k(k_arna_exchange, dim3((unsigned)m.G), dim3(256), s, m, b);
 }
@@ -3801,7 +3821,9 @@ hipError_t launch_anc(const Model& m, const Buffers& b, const WeightSrc& w, hipS
 
 hipError_t launch_rna(const Model& m, const Buffers& b, const WeightSrc& w, const double* u_dev,
                       hipStream_t s) {
-  return launch_k(k_rna, dim3((unsigned)m.G), dim3(256), s, m, b, w, u_dev);
+  if (m.group <= kWaveGroup)
+    return launch_k(k_rna<1>, dim3(grid_for(m.G, 4)), dim3(256), s, m, b, w, u_dev);
+  return launch_k(k_rna<4>, dim3((unsigned)m.G), dim3(256), s, m, b, w, u_dev);
 }
 
 hipError_t launch_gather(const Model& m, const Buffers& b, float* out, hipStream_t s) {
