@@ -274,7 +274,9 @@ int ppf_step(ppf_handle h, const float* obs_dev);
  * records the step's kernel launches into a HIP graph instead of launching
  * them, and that step and every later one launch the graph (hipGraphLaunch)
  * with its frame argument pointed at the call's obs_dev; results are the
- * same as without the graph. The launch sequence of a step does not depend
+ * same as without the graph. A step of at most 12 launches is launched
+ * directly all the same, which is the faster way to run it (RPA over more than
+ * 8192 groups takes more). The launch sequence of a step does not depend
  * on the filter's state (every decision is taken on the device), so one
  * recording serves all steps. Switching syncs the handle's stream and drops
  * the recorded graph. ESTATE while kernel timing (ppf_profile_enable) is on:

@@ -448,28 +448,46 @@ struct Runner {
     events.clear();
     return PPF_OK;
   }
-  // Graph mode: a step is recorded once into a HIP graph (the first step
-  // after enabling) and replayed, pointed at each call's frame.
+  // Graph mode: a step of more than kGraphLaunches launches is recorded once
+  // into a HIP graph (the first step
+  // after enabling) and replayed, pointed at each call's frame. A step of
+  // fewer is launched directly: a replay costs the host some 20 us and the GPU
+  // 5 us a step whatever it holds. Per step, host and in all, launched and
+  // replayed: 3 launches at 4096 particles 11 / 21 and 23 / 25 us, 4 at 2^20 14 /
+  // 44 and 18 / 49 us, 4 of RNA 16 / 60 and 20 / 65 us, 6 of 256 tracks 17 / 386
+  // and 48 / 390 us; 22 of RPA over sorted lists 70 / 124 and 35 / 127 us, where
+  // the replay at least leaves the host free.
+  static constexpr size_t kGraphLaunches = 12;
   bool graph_on = false;
+  bool graph_direct = false;  // this step's launches are too few
   std::unique_ptr<ppf::StepGraph> graph;
+  void drop_graph() {
+    graph.reset();
+    graph_direct = false;
+  }
   int graph_enable(int on) {
     if (on && prof) return fail(PPF_ESTATE, "graph mode and kernel timing exclude each other");
     if (hipStreamSynchronize(stream) != hipSuccess) return fail(PPF_EDEVICE, "sync");
     graph_on = on != 0;
-    graph.reset();
+    drop_graph();
     return PPF_OK;
   }
   // Enqueues one step: enqueue() itself, or the graph of its launches.
   template <class F>
   int step(const float* frame, F&& enqueue) {
-    if (!graph_on) return enqueue();
+    if (!graph_on || graph_direct) return enqueue();
     if (!graph) {
       auto g = std::make_unique<ppf::StepGraph>();
       hipError_t e = g->begin(frame);
       if (e != hipSuccess) return hip_fail(e, "hipGraphCreate");
       const int rc = enqueue();
-      e = g->end();
+      g->stop();
       if (rc) return rc;
+      if (g->launches() <= kGraphLaunches) {
+        graph_direct = true;
+        return enqueue();
+      }
+      e = g->instantiate();
       if (e != hipSuccess) return hip_fail(e, "hipGraphInstantiate");
       graph = std::move(g);
     }
@@ -703,7 +721,7 @@ int ppf_set_shape(ppf_handle h, int32_t shape) {
   const hipError_t e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return h->hip_fail(e, "sync");
   h->m.shape = shape;
-  h->graph.reset();
+  h->drop_graph();
   return PPF_OK;
 }
 
@@ -741,7 +759,7 @@ int ppf_autotune(ppf_handle h, const float* obs_dev, int32_t reps, double* ms_ou
   for (int c = 1; c < n; ++c)
     if (ms[c] < ms[best]) best = c;
   h->m.shape = shapes ? best : keep;
-  h->graph.reset();
+  h->drop_graph();
   tune_report(ms, n, best, ms_out, n_out, chosen);
   return PPF_OK;
 }
@@ -1151,7 +1169,7 @@ struct ppf_batch_ctx : Runner {
     plan.step_ranges = std::move(next.step_ranges);
     plan.shape_of = next.shape_of;
     candidate = cand;
-    graph.reset();
+    drop_graph();
     return PPF_OK;
   }
 };

@@ -309,7 +309,7 @@ hipError_t launch_rna_batch(const Model* ms, const Buffers* bs, const BatchItem*
                             int64_t n_items, hipStream_t s);
 
 // A HIP graph of one step's launches, replayed with another frame. While a
-// StepGraph records (begin() to end(), on the calling thread), the launch_*
+// StepGraph records (begin() to stop(), on the calling thread), the launch_*
 // functions above add kernel nodes to it, each depending on the one before,
 // instead of launching; the graph keeps every node's argument values, and
 // notes the arguments equal to the frame pointer given to begin() so that
@@ -321,7 +321,9 @@ class StepGraph {
   StepGraph& operator=(const StepGraph&) = delete;
   ~StepGraph();
   hipError_t begin(const float* frame);
-  hipError_t end();  // stops recording and instantiates the graph
+  void stop();
+  size_t launches() const { return nodes_.size(); }  // recorded
+  hipError_t instantiate();
   bool ready() const { return exec_ != nullptr; }
   hipError_t set_frame(const float* frame);
   hipError_t launch(hipStream_t s) const { return hipGraphLaunch(exec_, s); }

@@ -3445,10 +3445,12 @@ hipError_t StepGraph::begin(const float* frame) {
   return hipSuccess;
 }
 
-hipError_t StepGraph::end() {
-  if (t_rec != this) return hipErrorInvalidValue;
-  t_rec = nullptr;
-  if (nodes_.empty()) return hipErrorInvalidValue;
+void StepGraph::stop() {
+  if (t_rec == this) t_rec = nullptr;
+}
+
+hipError_t StepGraph::instantiate() {
+  if (t_rec == this || nodes_.empty()) return hipErrorInvalidValue;
   return hipGraphInstantiate(&exec_, graph_, nullptr, nullptr, 0);
 }
 
