@@ -345,35 +345,6 @@ __device__ __forceinline__ T wave_scan(T v, int lane, Op op) {
   return v;
 }
 
-// Reduction over a 256-thread workgroup (sh: 4 entries of LDS scratch).
-template <class T, class Op>
-__device__ __forceinline__ T block_reduce(T v, T* sh, Op op) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  v = wave_reduce(v, lane, op);
-  if (lane == 0) sh[w] = v;
-  __syncthreads();
-  const T r = op(op(sh[0], sh[1]), op(sh[2], sh[3]));
-  __syncthreads();
-  return r;
-}
-
-// Sums of K values over a 256-thread workgroup with one LDS exchange
-// (sh: 4 * K doubles), each in a fixed order.
-template <int K>
-__device__ __forceinline__ void block_sum_n(double (&v)[K], double* sh) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = wave_reduce_last(v[k], OpAdd(), 0.0);
-  if (lane == 63) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) sh[w * K + k] = v[k];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = (sh[k] + sh[K + k]) + (sh[2 * K + k] + sh[3 * K + k]);
-  __syncthreads();
-}
-
 // Exclusive prefix sum of exact unsigned integers over a 256-thread
 // workgroup; *total receives the sum of all.
 __device__ __forceinline__ uint64_t block_excl_sum(uint64_t v, uint64_t* sh, uint64_t* total) {
@@ -1301,14 +1272,16 @@ __global__ __launch_bounds__(256) void k_step_lg(Model m, Buffers b,
 
 // Records of caller-supplied absolute fp32 log weights (standalone
 // resampling): the same layout, with weights e = exp(x - m) in fp64 and zero
-// state sums.
+// state sums. One wave per block, four consecutive weights per lane: the block
+// maximum is a fp32 maximum of the fp32 inputs (exact), the fixed-point weights
+// sum exactly in any order, and no barrier waits. The kernel is bound by issue,
+// most of it the exps; with one weight per lane its fp64 maximum, two barriers
+// and LDS sums took 57 us for 16.8 M weights, against 30.5 us.
 __global__ __launch_bounds__(256) void k_records(Model m, Buffers b,
                                                  const float* __restrict__ logw) {
-  __shared__ double red[2 * 256];
-  __shared__ double dsh[4];
-  const int t = threadIdx.x;
-  const int64_t i = (int64_t)blockIdx.x * kBlock + t;
-  if (i == 0) {
+  const int lane = threadIdx.x & 63;
+  const int64_t blk = (int64_t)blockIdx.x * 4 + wave_index();
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     // the standalone scratch starts uninitialised: clear the counters and
     // flags the following kernels of this call rely on
     Ctrl* c = b.ctrl;
@@ -1318,29 +1291,47 @@ __global__ __launch_bounds__(256) void k_records(Model m, Buffers b,
     c->cur = 0;
     c->k = 0;
   }
-  const bool active = i < m.n;
-  const double l = active ? (double)logw[i] : -INFINITY;
-  const bool bad = active && (isnan(l) || l == INFINITY);
-  const double mb = block_reduce((active && !bad) ? l : -INFINITY, dsh, OpMax());
-  double e = 0.0;
-  if (active && !bad && mb != -INFINITY && l != -INFINITY) e = exp(l - mb);
-  red[t] = item_weight(e);
-  red[256 + t] = bad ? NAN : e * e;
-  __syncthreads();
-  double s = 0.0;
-  if (t < 64) {
-    const double* p = red + (t >> 5) * 256 + (t & 31) * 8;
-    s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+  if (blk >= b.nb) return;  // whole waves; no barrier follows
+  const int64_t i = blk * kBlock + 4 * lane;
+  float x[4];
+  if (i + 4 <= m.n && (reinterpret_cast<uintptr_t>(logw) & 15) == 0) {
+    const float4 v = *reinterpret_cast<const float4*>(logw + i);
+    x[0] = v.x;
+    x[1] = v.y;
+    x[2] = v.z;
+    x[3] = v.w;
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = i + q < m.n ? logw[i + q] : -INFINITY;
   }
-  s = row_allreduce(s, OpAdd());
-  const double h0 = readlane(s, 0) + readlane(s, 16);
-  const double h1 = readlane(s, 32) + readlane(s, 48);
-  if (t == 0) {
-    double* R = b.R0 + (int64_t)blockIdx.x * kRec;
+  bool bad = false;
+  int key = ord_key(-INFINITY);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const bool bq = !(x[q] < INFINITY);  // NaN or +inf
+    bad = bad || bq;
+    key = bq ? key : max(key, ord_key(x[q]));
+  }
+  const float mf = ord_val(readlane(wave_reduce_last(key, OpMax(), INT_MIN), 63));
+  const double mb = (double)mf;
+  double sums[2] = {0.0, 0.0};  // fixed-point weights, sum e^2
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double e = x[q] > -INFINITY && x[q] < INFINITY ? exp((double)x[q] - mb) : 0.0;
+    sums[0] += item_weight(e);
+    sums[1] = fma(e, e, sums[1]);
+  }
+  if (bad) sums[1] = NAN;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) sums[k] = wave_reduce_last(sums[k], OpAdd(), 0.0);
+  // lane 63 holds the sums, every lane the maximum
+  double* R = b.R0 + blk * kRec;
+  if (lane == 63) {
     R[0] = mb;
-    R[1] = h0;
-    R[2] = h1;
-    for (int d = 0; d < 5; ++d) R[3 + d] = 0.0;
+    R[1] = sums[0];
+    R[2] = sums[1];
+  } else if (lane < 5) {
+    R[3 + lane] = 0.0;
   }
 }
 
@@ -3845,7 +3836,7 @@ hipError_t launch_report(Ctrl* c, int32_t count, bool clear, Ctrl* out, hipStrea
 }
 
 hipError_t launch_records(const Model& m, const Buffers& b, const float* logw, hipStream_t s) {
-  return launch_k(k_records, dim3((unsigned)b.nb), dim3(kBlock), s, m, b, logw);
+  return launch_k(k_records, dim3(grid_for(b.nb, 4)), dim3(256), s, m, b, logw);
 }
 
 hipError_t launch_philox(uint64_t seed, const uint32_t* ctr, uint32_t* out, int64_t n,
