@@ -68,6 +68,8 @@ constexpr int kFillGridBatch = 2048;  // waves of a batched fill, over all track
 // sizes that fit five waves per SIMD); wider patches launch per size.
 constexpr int kFusedMaxP = 13;
 constexpr int kSortTile = 1024;      // pairs per tile of the list scans and of small sorts
+constexpr int64_t kSortFold = 1 << 19;   // pairs up to which the scatter adds up the tiles' counts
+constexpr unsigned kScanFold = 4096;  // list tiles up to which each adds up those before it
 constexpr int64_t kSortLarge = 1 << 22;  // pairs from which the radix sort takes 4096-pair tiles
 // RPA: up to kRankGroups groups are ranked by counting; up to kRpaScanN
 // particles the groups' offspring ranges are found by a look at every slot.

@@ -2678,7 +2678,11 @@ __device__ __forceinline__ void count_digit(uint32_t* h, uint32_t d, bool in) {
   }
 }
 
-template <int T, int R>
+// FOLD: few tiles; their counts stay a row per tile and every workgroup of the
+// scatter adds up the rows itself, for which a launch of its own takes longer
+// (304,000 pairs in 75 tiles of 4096: a pass 14.7 us in two launches, against 15.4
+// us and a gap in three over tiles of 1024).
+template <int T, int R, bool FOLD>
 __global__ __launch_bounds__(T) void k_radix_hist(const uint32_t* __restrict__ key, int64_t count,
                                                   int shift, uint32_t* __restrict__ hist,
                                                   int32_t ntiles, const Ctrl* gate) {
@@ -2698,7 +2702,7 @@ __global__ __launch_bounds__(T) void k_radix_hist(const uint32_t* __restrict__ k
 #pragma unroll
   for (int r = 0; r < R; ++r) count_digit(h, (k[r] >> shift) & 255u, base + r * T + t < count);
   __syncthreads();
-  if (t < 256) hist[(int64_t)t * ntiles + tile] = h[t];
+  if (t < 256) hist[FOLD ? (int64_t)tile * 256 + t : (int64_t)t * ntiles + tile] = h[t];
 }
 
 __global__ __launch_bounds__(256) void k_radix_rowscan(uint32_t* __restrict__ hist, int32_t ntiles,
@@ -2731,7 +2735,7 @@ __global__ __launch_bounds__(256) void k_radix_rowscan(uint32_t* __restrict__ hi
 
 // vin null: the values are the pairs' positions. kout null: the keys are not
 // needed any more.
-template <int T, int R>
+template <int T, int R, bool FOLD>
 __global__ __launch_bounds__(T) void k_radix_scatter(
     const uint32_t* __restrict__ kin, const int32_t* __restrict__ vin, uint32_t* __restrict__ kout,
     int32_t* __restrict__ vout, int64_t count, int shift, const uint32_t* __restrict__ hist,
@@ -2758,10 +2762,30 @@ __global__ __launch_bounds__(T) void k_radix_scatter(
     key[r] = kin[j];
     val[r] = vin ? vin[j] : (int32_t)j;
   }
-  const uint32_t dtot = t < 256 ? rowtot[t] : 0;
-  const uint32_t before = t < 256 ? hist[(int64_t)t * ntiles + tile] : 0;
+  // the digit's pairs in all tiles, and in the tiles before this one
+  uint32_t dtot = 0, before = 0;
+  constexpr int kParts = T / 256;  // FOLD: threads that share a digit's rows
+  if (FOLD) {
+    static_assert(!FOLD || 2 * T <= kTile, "the partial sums go through skey");
+    for (int i0 = t >> 8; i0 < ntiles; i0 += 16 * kParts) {
+      uint32_t c[16];
 #pragma unroll
-  for (int q = 0; q < kWaves * 256 / T; ++q) wcnt[0][q * T + t] = 0;
+      for (int i = 0; i < 16; ++i)
+        c[i] = hist[(int64_t)min(i0 + i * kParts, ntiles - 1) * 256 + (t & 255)];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        dtot += i0 + i * kParts < ntiles ? c[i] : 0;
+        before += i0 + i * kParts < tile ? c[i] : 0;
+      }
+    }
+    skey[t] = dtot;
+    skey[T + t] = before;
+  } else if (t < 256) {
+    dtot = rowtot[t];
+    before = hist[(int64_t)t * ntiles + tile];
+  }
+#pragma unroll
+  for (int q = 0; q < 256 / 64; ++q) wcnt[0][q * T + t] = 0;
   __syncthreads();
   uint32_t pos[R];  // rank among the wave's pairs of the same digit
 #pragma unroll
@@ -2781,6 +2805,14 @@ __global__ __launch_bounds__(T) void k_radix_scatter(
   __syncthreads();
   uint32_t tcnt = 0, li = 0, gi = 0;
   if (t < 256) {  // whole waves
+    if (FOLD) {
+      dtot = before = 0;
+#pragma unroll
+      for (int q = 0; q < kParts; ++q) {
+        dtot += skey[q * 256 + t];
+        before += skey[T + q * 256 + t];
+      }
+    }
 #pragma unroll
     for (int ww = 0; ww < kWaves; ++ww) {
       const uint32_t c = wcnt[ww][t];
@@ -3000,8 +3032,10 @@ __global__ __launch_bounds__(256) void k_rpa_route(Model m, Buffers b) {
 // (descending, ties in group order); absent entries sort last in their side.
 __global__ __launch_bounds__(256) void k_dlb_keys(int32_t kind, const int32_t* __restrict__ counts,
                                                   int32_t G, int32_t n, uint32_t* __restrict__ key,
-                                                  int32_t* __restrict__ val) {
+                                                  int32_t* __restrict__ val,
+                                                  int32_t* __restrict__ nsr) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (j < 2) nsr[j] = 0;
   if (j >= 2 * (int64_t)G) return;
   const int side = j >= G ? 1 : 0;
   const int64_t g = j - side * (int64_t)G;
@@ -3013,41 +3047,26 @@ __global__ __launch_bounds__(256) void k_dlb_keys(int32_t kind, const int32_t* _
   val[j] = (int32_t)g;
 }
 
-__global__ __launch_bounds__(64) void k_zero_i32(int32_t* __restrict__ p, int32_t count) {
-  if ((int32_t)threadIdx.x < count) p[threadIdx.x] = 0;
+// The lists' prefixes, per side, and later the senders' entries': the tiles' sums
+// in one launch with whatever makes the values, the prefixes in the next, where
+// each workgroup adds up the tiles before its own
+// (kScanFold of them at most; beyond, k_scan_top does it once). With the lists'
+// sort in eight launches instead of twelve, a schedule of 152,000 groups takes 14
+// launches and 94 us of kernels against 27 and 122 us.
+
+// The sum of the tile sums before `tile` (its prefix already, when `scanned`).
+__device__ __forceinline__ uint64_t tiles_before(const uint64_t* __restrict__ tsum, int64_t tile,
+                                                 bool scanned, uint64_t* sh) {
+  if (scanned) return tsum[tile];
+  uint64_t s = 0, total;
+  for (int64_t i = threadIdx.x; i < tile; i += 256) s += tsum[i];
+  block_excl_sum(s, sh, &total);
+  return total;
 }
 
-// The surplus (side 0) or deficit (side 1) at each list position, 0 past
-// the present entries.
-__global__ __launch_bounds__(256) void k_dlb_values(const int32_t* __restrict__ counts, int32_t G,
-                                                    int32_t n, const int32_t* __restrict__ val,
-                                                    uint64_t* __restrict__ vals) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j >= 2 * (int64_t)G) return;
-  const int side = j >= G ? 1 : 0;
-  const int64_t c = counts[val[j]];
-  const int64_t v = side == 0 ? c - n : n - c;
-  vals[j] = v > 0 ? (uint64_t)v : 0;
-}
-
-// Exclusive prefix sums over `len` uint64 values (tiles of kSortTile: the
-// tiles' sums, their prefixes in one workgroup, then each value's prefix);
-// out[len] receives the total.
-__global__ __launch_bounds__(256) void k_scan_tiles(const uint64_t* __restrict__ in, int64_t len,
-                                                    uint64_t* __restrict__ tsum) {
+__global__ __launch_bounds__(256) void k_scan_top(uint64_t* __restrict__ tsum, int64_t ntiles) {
   __shared__ uint64_t sh[4];
-  const int64_t k0 = (int64_t)blockIdx.x * kSortTile + 4 * threadIdx.x;
-  uint64_t s = 0;
-  for (int i = 0; i < 4; ++i)
-    if (k0 + i < len) s += in[k0 + i];
-  uint64_t tot;
-  block_excl_sum(s, sh, &tot);
-  if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(256) void k_scan_top(uint64_t* __restrict__ tsum, int64_t ntiles,
-                                                  uint64_t* __restrict__ total) {
-  __shared__ uint64_t sh[4];
+  tsum += blockIdx.x * ntiles;
   uint64_t carry = 0;
   for (int64_t i0 = 0; i0 < ntiles; i0 += 256) {
     const int64_t i = i0 + threadIdx.x;
@@ -3057,71 +3076,157 @@ __global__ __launch_bounds__(256) void k_scan_top(uint64_t* __restrict__ tsum, i
     if (i < ntiles) tsum[i] = carry + ex;
     carry += t;
   }
-  if (threadIdx.x == 0) *total = carry;
 }
 
-__global__ __launch_bounds__(256) void k_scan_apply(const uint64_t* __restrict__ in, int64_t len,
-                                                    const uint64_t* __restrict__ tsum,
-                                                    uint64_t* __restrict__ out) {
-  __shared__ uint64_t sh[4];
-  const int64_t k0 = (int64_t)blockIdx.x * kSortTile + 4 * threadIdx.x;
-  uint64_t v[4], s = 0;
-  for (int i = 0; i < 4; ++i) {
+// Exclusive prefixes of tile `tile`'s 256 PER values into out, by the last tile
+// the total into out[len].
+template <int PER>
+__device__ __forceinline__ void scan_tile(const uint64_t* __restrict__ in, int64_t len,
+                                          const uint64_t* __restrict__ tsum, int64_t tile,
+                                          bool scanned, uint64_t* __restrict__ out) {
+  __shared__ uint64_t sh[4], sh2[4];
+  const int64_t k0 = (tile * 256 + threadIdx.x) * PER;
+  uint64_t v[PER], s = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
     v[i] = k0 + i < len ? in[k0 + i] : 0;
     s += v[i];
   }
+  const uint64_t base = tiles_before(tsum, tile, scanned, sh2);
   uint64_t tot;
-  uint64_t p = block_excl_sum(s, sh, &tot) + tsum[blockIdx.x];
-  for (int i = 0; i < 4; ++i) {
+  uint64_t p = base + block_excl_sum(s, sh, &tot);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
     if (k0 + i < len) out[k0 + i] = p;
     p += v[i];
   }
+  if (threadIdx.x == 0 && (tile + 1) * 256 * PER >= len) out[len] = base + tot;
 }
 
-// Number of the leading positive values of one side (its present entries).
-__global__ __launch_bounds__(256) void k_dlb_present(const uint64_t* __restrict__ vals, int32_t G,
-                                                     int32_t* __restrict__ nsr) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j >= 2 * (int64_t)G) return;
-  const int side = j >= G ? 1 : 0;
-  const int64_t k = j - side * (int64_t)G;
-  // present entries come first: the last one marks the count
-  if (vals[j] > 0 && (k + 1 == G || vals[j + 1] == 0)) nsr[side] = (int32_t)(k + 1);
+// The surplus (side 0) or deficit (side 1) at each list position, 0 past the
+// present entries, with their tile sums; the present entries come first, so the
+// last one marks their number (none: k_dlb_keys has left 0).
+__global__ __launch_bounds__(256) void k_dlb_values(const int32_t* __restrict__ counts, int32_t G,
+                                                    int32_t n, const int32_t* __restrict__ val,
+                                                    uint64_t* __restrict__ vals,
+                                                    uint64_t* __restrict__ tsum,
+                                                    int32_t* __restrict__ nsr) {
+  __shared__ uint64_t sh[4];
+  const int side = blockIdx.y;
+  const int64_t k0 = (int64_t)blockIdx.x * kSortTile + 4 * threadIdx.x;
+  const int32_t* lv = val + side * (int64_t)G;
+  int64_t c[5];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) c[i] = lv[min(k0 + i, (int64_t)G - 1)];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) c[i] = counts[c[i]];
+  uint64_t v[5], s = 0;
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const int64_t d = side == 0 ? c[i] - n : n - c[i];
+    v[i] = k0 + i < G && d > 0 ? (uint64_t)d : 0;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (k0 + i < G) vals[side * (int64_t)G + k0 + i] = v[i];
+    if (v[i] > 0 && v[i + 1] == 0) nsr[side] = (int32_t)(k0 + i + 1);
+    s += v[i];
+  }
+  uint64_t tot;
+  block_excl_sum(s, sh, &tot);
+  if (threadIdx.x == 0) tsum[side * (int64_t)gridDim.x + blockIdx.x] = tot;
+}
+
+__global__ __launch_bounds__(256) void k_dlb_prefix(const uint64_t* __restrict__ vals, int32_t G,
+                                                    const uint64_t* __restrict__ tsum,
+                                                    int32_t scanned, uint64_t* __restrict__ cs,
+                                                    uint64_t* __restrict__ cd) {
+  const int side = blockIdx.y;
+  scan_tile<kSortTile / 256>(vals + side * (int64_t)G, G, tsum + side * (int64_t)gridDim.x, blockIdx.x,
+            scanned != 0, side ? cd : cs);
+}
+
+__global__ __launch_bounds__(256) void k_dlb_entry_prefix(const uint64_t* __restrict__ cnt,
+                                                          int32_t G,
+                                                          const uint64_t* __restrict__ tsum,
+                                                          int32_t scanned,
+                                                          uint64_t* __restrict__ E) {
+  scan_tile<1>(cnt, G, tsum, blockIdx.x, scanned != 0, E);
+}
+
+// The last j in [lo, hi] with a[j] <= v, a non-decreasing and a[lo] <= v: by one
+// lane, or by the whole wave 64 ways at a time (v uniform).
+__device__ __forceinline__ int64_t last_le(const uint64_t* a, int64_t lo, int64_t hi,
+                                           uint64_t v) {
+  while (lo < hi) {
+    const int64_t mid = (lo + hi + 1) >> 1;
+    if (a[mid] <= v) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+// The same by steps that double from lo, for a j that is near it.
+__device__ __forceinline__ int64_t last_le_near(const uint64_t* a, int64_t lo, int64_t hi,
+                                                uint64_t v) {
+  int64_t step = 1;
+  while (lo + step <= hi && a[lo + step] <= v) {
+    lo += step;
+    step *= 2;
+  }
+  return last_le(a, lo, min(hi, lo + step - 1), v);
+}
+__device__ __forceinline__ int64_t wave_last_le(const uint64_t* __restrict__ a, int64_t lo,
+                                                int64_t hi, uint64_t v) {
+  const int lane = threadIdx.x & 63;
+  while (lo < hi) {  // uniform
+    const int64_t step = (hi - lo + 63) / 64, p = lo + (lane + 1) * step;
+    const bool le = p <= hi && a[min(p, hi)] <= v;
+    lo += __popcll(__ballot(le)) * step;
+    hi = min(hi, lo + step - 1);
+  }
+  return lo;
 }
 
 // GS / SGS: the greedy walk of the two lists (Alg. 2, with filled receivers
 // skipped) pairs sender i with every receiver whose deficit interval
 // [cd_j, cd_j + de_j) overlaps its surplus interval [cs_i, cs_i + su_i),
 // both laid end to end in list order and cut at T = min(total surplus,
-// total deficit). Per sender: its first receiver and its number of entries.
+// total deficit). Per sender: its first receiver and its number of entries;
+// per workgroup's 256 senders their sum. A workgroup's senders meet a short range
+// of receivers, which one wave finds 64 ways at a time before each sender searches
+// it (a search of the whole list by every thread is a chain of 17 loads).
 __global__ __launch_bounds__(256) void k_dlb_count(const uint64_t* __restrict__ cs,
                                                    const uint64_t* __restrict__ cd,
                                                    const int32_t* __restrict__ nsr, int32_t G,
                                                    int32_t* __restrict__ jlo,
-                                                   uint64_t* __restrict__ cnt) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= G) return;
+                                                   uint64_t* __restrict__ cnt,
+                                                   uint64_t* __restrict__ tsum) {
+  __shared__ uint64_t sh[4];
+  __shared__ int64_t range[2];
+  const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + threadIdx.x;
   const int64_t ns = nsr[0], nr = nsr[1];
   const uint64_t T = min(cs[ns], cd[nr]);
-  cnt[i] = 0;
-  if (i >= ns || cs[i] >= T) return;
-  const uint64_t* d = cd;
-  // last j with d[j] <= cs[i], then last j with d[j] < min(cs[i + 1], T)
-  int64_t lo = 0, hi = nr - 1;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi + 1) >> 1;
-    if (d[mid] <= cs[i]) lo = mid;
-    else hi = mid - 1;
+  const int64_t i1 = min(i0 + 256, ns);  // the workgroup's present senders end here
+  const uint64_t c0 = cs[min(i, ns)], c1 = min(cs[min(i + 1, ns)], T);
+  if (i0 < i1 && nr > 0 && wave_index() < 2) {  // uniform
+    const uint64_t v = wave_index() == 0 ? cs[i0] : min(cs[i1], T) - 1;
+    const int64_t r = cs[i0] < T ? wave_last_le(cd, 0, nr - 1, v) : 0;
+    if ((threadIdx.x & 63) == 0) range[wave_index()] = r;
   }
-  const uint64_t end = min(cs[i + 1], T);
-  int64_t lo2 = lo, hi2 = nr - 1;
-  while (lo2 < hi2) {
-    const int64_t mid = (lo2 + hi2 + 1) >> 1;
-    if (d[mid] < end) lo2 = mid;
-    else hi2 = mid - 1;
+  __syncthreads();
+  uint64_t n_e = 0;
+  if (i < ns && c0 < T) {
+    // last j with d[j] <= cs[i], then last j with d[j] < min(cs[i + 1], T),
+    // which is near it
+    const int64_t lo = last_le(cd, range[0], range[1], c0);
+    const int64_t hi = last_le_near(cd, lo, range[1], c1 - 1);
+    jlo[i] = (int32_t)lo;
+    n_e = (uint64_t)(hi - lo + 1);
   }
-  jlo[i] = (int32_t)lo;
-  cnt[i] = (uint64_t)(lo2 - lo + 1);
+  if (i < G) cnt[i] = n_e;
+  uint64_t tot;
+  block_excl_sum(n_e, sh, &tot);
+  if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
 }
 
 // Entry e: GS / SGS its sender (the last with entry prefix <= e) and
@@ -3137,11 +3242,20 @@ __global__ __launch_bounds__(256) void k_dlb_entries(int32_t kind, const int32_t
                                                      const uint64_t* __restrict__ E,
                                                      int32_t* __restrict__ sched, int32_t cap,
                                                      int32_t* __restrict__ n_entries) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  __shared__ int64_t range[2];
+  const int64_t e0 = (int64_t)blockIdx.x * 256, e = e0 + threadIdx.x;
   const int64_t ns = nsr[0], nr = nsr[1];
   const int64_t M = kind == 2 ? min(ns, nr) : (int64_t)E[G];
   if (e == 0) *n_entries = M <= cap ? (int32_t)M : -1;
-  if (e >= M || M > cap) return;  // nothing is written past the capacity
+  if (e0 >= M || M > cap) return;  // uniform; nothing is written past the capacity
+  if (kind != 2 && wave_index() < 2) {
+    // the senders of the workgroup's first and last entries
+    const int64_t r =
+        wave_last_le(E, 0, ns - 1, (uint64_t)(wave_index() == 0 ? e0 : min(e0 + 255, M - 1)));
+    if ((threadIdx.x & 63) == 0) range[wave_index()] = r;
+  }
+  __syncthreads();
+  if (e >= M) return;
   int64_t i, j;
   uint64_t amount;
   if (kind == 2) {
@@ -3149,13 +3263,7 @@ __global__ __launch_bounds__(256) void k_dlb_entries(int32_t kind, const int32_t
     j = e;
     amount = min(vals[i], vals[G + j]);
   } else {
-    int64_t lo = 0, hi = ns - 1;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi + 1) >> 1;
-      if (E[mid] <= (uint64_t)e) lo = mid;
-      else hi = mid - 1;
-    }
-    i = lo;
+    i = last_le(E, range[0], range[1], (uint64_t)e);
     j = jlo[i] + (e - (int64_t)E[i]);
     const uint64_t* d = cd;
     const uint64_t T = min(cs[ns], d[nr]);
@@ -3535,11 +3643,11 @@ namespace {
 // even ones and back on odd ones, so the result lands in ping (v0; the last
 // pass leaves the keys unwritten). positions: the values start as the pairs'
 // positions instead of v0.
-template <int T, int R>
+template <int T, int R, bool FOLD>
 hipError_t radix_sort_tiles(uint32_t* k0, uint32_t* k1, int32_t* v0, int32_t* v1, uint32_t* hist,
                             uint32_t* row, int64_t count, bool positions, const Ctrl* gate,
                             hipStream_t s) {
-  static_assert(T * R >= kSortTile, "the digit counts hold a column per kSortTile pairs");
+  static_assert(T * R >= kSortTile, "the digit counts hold 256 per kSortTile pairs");
   const int32_t nt = (int32_t)((count + T * R - 1) / (T * R));
   hipError_t e = hipSuccess;
   for (int pass = 0; pass < 4 && e == hipSuccess; ++pass) {
@@ -3547,13 +3655,13 @@ hipError_t radix_sort_tiles(uint32_t* k0, uint32_t* k1, int32_t* v0, int32_t* v1
     const int32_t* vin = pass & 1 ? v1 : (pass == 0 && positions ? nullptr : v0);
     uint32_t* kout = pass == 3 ? nullptr : (pass & 1 ? k0 : k1);
     int32_t* vout = pass & 1 ? v0 : v1;
-    e = launch_k(k_radix_hist<T, R>, dim3((unsigned)nt), dim3(T), s, kin, count, 8 * pass, hist,
-                 nt, gate);
-    if (e == hipSuccess)
+    e = launch_k(k_radix_hist<T, R, FOLD>, dim3((unsigned)nt), dim3(T), s, kin, count, 8 * pass,
+                 hist, nt, gate);
+    if (e == hipSuccess && !FOLD)
       e = launch_k(k_radix_rowscan, dim3(256), dim3(256), s, hist, nt, row, gate);
     if (e == hipSuccess)
-      e = launch_k(k_radix_scatter<T, R>, dim3((unsigned)nt), dim3(T), s, kin, vin, kout, vout,
-                   count, 8 * pass, (const uint32_t*)hist, (const uint32_t*)row, nt, gate);
+      e = launch_k(k_radix_scatter<T, R, FOLD>, dim3((unsigned)nt), dim3(T), s, kin, vin, kout,
+                   vout, count, 8 * pass, (const uint32_t*)hist, (const uint32_t*)row, nt, gate);
   }
   return e;
 }
@@ -3562,8 +3670,10 @@ hipError_t radix_sort(uint32_t* k0, uint32_t* k1, int32_t* v0, int32_t* v1, uint
                       uint32_t* row, int64_t count, bool positions, const Ctrl* gate,
                       hipStream_t s) {
   if (count >= kSortLarge)
-    return radix_sort_tiles<256, 16>(k0, k1, v0, v1, hist, row, count, positions, gate, s);
-  return radix_sort_tiles<256, 4>(k0, k1, v0, v1, hist, row, count, positions, gate, s);
+    return radix_sort_tiles<256, 16, false>(k0, k1, v0, v1, hist, row, count, positions, gate, s);
+  if (count > kSortFold)
+    return radix_sort_tiles<256, 4, false>(k0, k1, v0, v1, hist, row, count, positions, gate, s);
+  return radix_sort_tiles<1024, 4, true>(k0, k1, v0, v1, hist, row, count, positions, gate, s);
 }
 }  // namespace
 
@@ -3707,7 +3817,7 @@ struct DlbScratch {
   uint64_t* cnt;   // entries per sender, G
   uint64_t* E;     // their prefixes, G + 1
   int32_t* jlo;    // each sender's first receiver, G
-  uint64_t* tsum;  // scan tiles
+  uint64_t* tsum;  // tile sums: 2 per 1024 list positions, or 1 per 256 senders
   int32_t* nsr;    // present entries per side, 2
 };
 
@@ -3731,21 +3841,11 @@ size_t dlb_carve(int32_t G, char* base, DlbScratch* d) {
   d->cnt = reinterpret_cast<uint64_t*>(take((size_t)G * 8));
   d->E = reinterpret_cast<uint64_t*>(take(((size_t)G + 1) * 8));
   d->jlo = reinterpret_cast<int32_t*>(take((size_t)G * 4));
-  d->tsum = reinterpret_cast<uint64_t*>(take((nt + 1) * 8));
+  d->tsum = reinterpret_cast<uint64_t*>(take(((size_t)G / 256 + 2) * 8));
   d->nsr = reinterpret_cast<int32_t*>(take(2 * 4));
   return off;
 }
 
-// Exclusive prefix sums of len values into out[0..len), the total into
-// out[len] (tsum: scan tiles).
-hipError_t scan_u64(const uint64_t* in, int64_t len, uint64_t* out, uint64_t* tsum, hipStream_t s) {
-  const unsigned nt = (unsigned)((len + kSortTile - 1) / kSortTile);
-  hipError_t e = launch_k(k_scan_tiles, dim3(nt), dim3(256), s, in, len, tsum);
-  if (e == hipSuccess) e = launch_k(k_scan_top, dim3(1), dim3(256), s, tsum, (int64_t)nt, out + len);
-  if (e == hipSuccess)
-    e = launch_k(k_scan_apply, dim3(nt), dim3(256), s, in, len, (const uint64_t*)tsum, out);
-  return e;
-}
 }  // namespace
 
 size_t dlb_scratch_bytes(int32_t G) {
@@ -3759,24 +3859,31 @@ hipError_t launch_dlb_schedule(int32_t kind, const int32_t* counts, int32_t G, i
   const int64_t L = 2 * (int64_t)G;
   DlbScratch d;
   dlb_carve(G, static_cast<char*>(scratch), &d);
+  const unsigned nt = (unsigned)(((int64_t)G + kSortTile - 1) / kSortTile);
+  const int32_t scanned = nt > kScanFold ? 1 : 0;
   hipError_t e = launch_k(k_dlb_keys, dim3(grid_for(L, 256)), dim3(256), s, kind, counts, G, n,
-                          d.key0, d.val0);
+                          d.key0, d.val0, d.nsr);
   if (e == hipSuccess)
     e = radix_sort(d.key0, d.key1, d.val0, d.val1, d.hist, d.row, L, false, nullptr, s);
   if (e == hipSuccess)
-    e = launch_k(k_dlb_values, dim3(grid_for(L, 256)), dim3(256), s, counts, G, n,
-                 (const int32_t*)d.val0, d.vals);
-  if (e == hipSuccess) e = launch_k(k_zero_i32, dim3(1), dim3(64), s, d.nsr, 2);
+    e = launch_k(k_dlb_values, dim3(nt, 2), dim3(256), s, counts, G, n, (const int32_t*)d.val0,
+                 d.vals, d.tsum, d.nsr);
+  if (e == hipSuccess && scanned)
+    e = launch_k(k_scan_top, dim3(2), dim3(256), s, d.tsum, (int64_t)nt);
   if (e == hipSuccess)
-    e = launch_k(k_dlb_present, dim3(grid_for(L, 256)), dim3(256), s, (const uint64_t*)d.vals, G,
-                 d.nsr);
-  if (e == hipSuccess) e = scan_u64(d.vals, G, d.cs, d.tsum, s);
-  if (e == hipSuccess) e = scan_u64(d.vals + G, G, d.cd, d.tsum, s);
+    e = launch_k(k_dlb_prefix, dim3(nt, 2), dim3(256), s, (const uint64_t*)d.vals, G,
+                 (const uint64_t*)d.tsum, scanned, d.cs, d.cd);
   if (kind != 2) {
+    const unsigned nw = grid_for(G, 256);
+    const int32_t scanned_e = nw > kScanFold ? 1 : 0;
     if (e == hipSuccess)
-      e = launch_k(k_dlb_count, dim3(grid_for(G, 256)), dim3(256), s, (const uint64_t*)d.cs,
-                   (const uint64_t*)d.cd, (const int32_t*)d.nsr, G, d.jlo, d.cnt);
-    if (e == hipSuccess) e = scan_u64(d.cnt, G, d.E, d.tsum, s);
+      e = launch_k(k_dlb_count, dim3(nw), dim3(256), s, (const uint64_t*)d.cs,
+                   (const uint64_t*)d.cd, (const int32_t*)d.nsr, G, d.jlo, d.cnt, d.tsum);
+    if (e == hipSuccess && scanned_e)
+      e = launch_k(k_scan_top, dim3(1), dim3(256), s, d.tsum, (int64_t)nw);
+    if (e == hipSuccess)
+      e = launch_k(k_dlb_entry_prefix, dim3(nw), dim3(256), s, (const uint64_t*)d.cnt, G,
+                   (const uint64_t*)d.tsum, scanned_e, d.E);
   }
   if (e == hipSuccess)
     e = launch_k(k_dlb_entries, dim3(grid_for(L, 256)), dim3(256), s, kind,
