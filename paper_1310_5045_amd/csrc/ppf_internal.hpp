@@ -14,8 +14,8 @@ namespace ppf {
 // normalisation records and of the stored log-weight offsets.
 constexpr int kBlock = 256;
 // LDS image tile of one k_step workgroup (D = Z - b as doubles; this is the
-// widest) and its table of P-pixel row sums of D^2 at the patch-centre
-// columns (doubles).
+// widest) and gradient mode's tables of P-pixel row sums of D^2 and of D at the
+// patch-centre columns (doubles).
 constexpr int kTileCap = 2048;
 constexpr int kSqCap = 1536;
 // Workgroup shapes of the step kernel for patches up to kFusedMaxP: shape s
@@ -183,7 +183,7 @@ struct Model {
   int32_t shape;         // step workgroup shape (patches up to kFusedMaxP)
   double s_psf;          // s
   double sig;            // sigma_xi
-  double clo[2], chi[2]; // patch-centre clamp (x, y): -P and W + P, H + P
+  double is2;            // 1 / s^2
   // ARNA (group, G and moved = the largest exchange as for RNA)
   int32_t arna;          // adaptive RNA
   int32_t arna_mu_min;   // the smallest exchange, floor(arna_min n)

@@ -114,16 +114,21 @@ __device__ __forceinline__ float cos_halfpi(float r2) {
   return fmaf(p, r2, 1.0f);
 }
 
+// v, negated when bit 1 of the quadrant q is set.
+__device__ __forceinline__ float with_sign_of_bit1(float v, int q) {
+  return __uint_as_float(__float_as_uint(v) ^ (((uint32_t)q << 30) & 0x80000000u));
+}
+
 __device__ __forceinline__ void box_muller(uint32_t rf, uint32_t af, float& z0, float& z1) {
   const float rad = bm_radius(rf);
   const float x = (float)af * 0x1p-16f;  // 4 t, exact
   const float q = rintf(x);
   const float r = x - q, r2 = r * r;
   const float sn = sin_halfpi(r, r2), cs = cos_halfpi(r2);
-  const int qi = (int)q & 3;
+  const int qi = (int)q;
   const float ss = (qi & 1) ? cs : sn, cc = (qi & 1) ? sn : cs;
-  z0 = rad * (((qi + 1) & 2) ? -cc : cc);
-  z1 = rad * ((qi & 2) ? -ss : ss);
+  z0 = rad * with_sign_of_bit1(cc, qi + 1);
+  z1 = rad * with_sign_of_bit1(ss, qi);
 }
 
 // The cosine branch alone.
@@ -132,9 +137,9 @@ __device__ __forceinline__ float box_muller_cos(uint32_t rf, uint32_t af) {
   const float x = (float)af * 0x1p-16f;
   const float q = rintf(x);
   const float r = x - q, r2 = r * r;
-  const int qi = (int)q & 3;
+  const int qi = (int)q;
   const float cc = (qi & 1) ? sin_halfpi(r, r2) : cos_halfpi(r2);
-  return rad * (((qi + 1) & 2) ? -cc : cc);
+  return rad * with_sign_of_bit1(cc, qi + 1);
 }
 
 __device__ __forceinline__ void box_muller64(uint32_t r, uint32_t a, double& z0, double& z1) {
@@ -143,6 +148,20 @@ __device__ __forceinline__ void box_muller64(uint32_t r, uint32_t a, double& z0,
   sincospi((double)a * 0x1p-17, &s, &c);  // 2 t
   z0 = rad * c;
   z1 = rad * s;
+}
+
+// x as an integer, saturated to the int range (NaN reads as 0).
+__device__ __forceinline__ int cvt_sat_i32(double x) {
+  int r;
+  asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+
+// A constant kept in scalar registers: the compiler otherwise moves it into a
+// vector register pair before each fused multiply-add that overwrites it.
+__device__ __forceinline__ double sconst(double c) {
+  asm("" : "+s"(c));
+  return c;
 }
 
 // e^x for finite x: Cody-Waite reduction x = k ln2 + r with ln 2 split into
@@ -165,7 +184,7 @@ __device__ __forceinline__ double exp_fast(double x) {
   p = fma(p, r, 0.5);
   p = fma(p, r, 1.0);
   p = fma(p, r, 1.0);
-  return ldexp(p, (int)fmax(fmin(k, 2100.0), -2100.0));
+  return ldexp(p, cvt_sat_i32(k));
 }
 
 // ------------------------------------------------------ wave64 primitives
@@ -232,15 +251,6 @@ struct OpMax {
 struct OpMin {
   __device__ __forceinline__ int operator()(int a, int b) const { return a < b ? a : b; }
 };
-// Elementwise minimum of two int16 pairs packed in 32 bits (v_pk_min_i16).
-struct OpMin16x2 {
-  __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const {
-    typedef short s2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(s2, a),
-                                                                  __builtin_bit_cast(s2, b)));
-  }
-};
-
 // Inclusive scan within each row of 16 lanes (r = lane & 15).
 template <class T, class Op>
 __device__ __forceinline__ T row_scan(T v, int r, Op op) {
@@ -284,10 +294,6 @@ __device__ __forceinline__ uint32_t bcast32(uint32_t v, uint32_t id) {
 template <int CTRL, int ROWS>
 __device__ __forceinline__ int bcast(int v, int id) {
   return (int)bcast32<CTRL, ROWS>((uint32_t)v, (uint32_t)id);
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t bcast(uint32_t v, uint32_t id) {
-  return bcast32<CTRL, ROWS>(v, id);
 }
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double bcast(double v, double id) {
@@ -504,17 +510,40 @@ __device__ __forceinline__ double prior_lw(const Model& m, const Buffers& b, int
   return -m.log_n;
 }
 
-// zo (5 normals) and po (the parent) are optional outputs for the tangents.
+// Addresses of a block's particles: a wave-uniform base and the thread's index in
+// the block, so that an access needs no 64-bit vector arithmetic.
+//
+// Particle base + t of a block; zo (5 normals) and po (the parent) are optional
+// outputs for the tangents.
 __device__ __forceinline__ Prop propagate(const Model& m, const Buffers& b, int cur, int mode,
-                                          int64_t i, uint32_t k, float* zo = nullptr,
-                                          int64_t* po = nullptr) {
+                                          int64_t base, uint32_t t, uint32_t k,
+                                          float* zo = nullptr, int64_t* po = nullptr) {
   const float* Xin = cur ? b.X1 : b.X0;
-  int64_t p = i;
-  if (mode == kModeSys || mode == kModeRna || mode == kModeArna) p = b.anc[i];
+  const uint32_t i = (uint32_t)base + t;  // particle indices are below 2^31
+  uint32_t p = i;
+  if (mode == kModeSys || mode == kModeRna || mode == kModeArna)
+    p = (uint32_t)(b.anc + base)[t];
   const int64_t n = m.n;
-  const float px = Xin[p], py = Xin[n + p], pvx = Xin[2 * n + p], pvy = Xin[3 * n + p],
-              pI = Xin[4 * n + p];
-  const NormalFields nf = normal_fields(draw(m, (uint32_t)i, k, kPropagate, 0u));
+  float px, py, pvx, pvy, pI;
+  if (n <= (int64_t)1 << 30) {  // uniform: byte offsets of 32 bits
+    auto at = [&](int d) {
+      return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Xin + d * n) + 4u * p);
+    };
+    px = at(0);
+    py = at(1);
+    pvx = at(2);
+    pvy = at(3);
+    pI = at(4);
+  } else {
+    px = Xin[p];
+    py = Xin[n + p];
+    pvx = Xin[2 * n + p];
+    pvy = Xin[3 * n + p];
+    pI = Xin[4 * n + p];
+    // (keeps the compiler from folding the two ways into this one)
+    asm volatile("" : "+v"(px), "+v"(py), "+v"(pvx), "+v"(pvy), "+v"(pI));
+  }
+  const NormalFields nf = normal_fields(draw(m, i, k, kPropagate, 0u));
   float z0, z1, z2, z3;
   box_muller(nf.r0, nf.a0, z0, z1);
   box_muller(nf.r1, nf.a1, z2, z3);
@@ -526,7 +555,7 @@ __device__ __forceinline__ Prop propagate(const Model& m, const Buffers& b, int 
     zo[3] = z3;
     zo[4] = z4;
   }
-  if (po) *po = p;
+  if (po) *po = (int64_t)p;
   Prop o;
   // near-constant velocity, unit frame interval; in fp32 with one fused
   // multiply-add per component, the small velocity and noise terms first,
@@ -544,15 +573,15 @@ __device__ __forceinline__ Prop propagate(const Model& m, const Buffers& b, int 
 // step gathers them through the ancestors long after, and left in the
 // caches as dirty lines their write-back would compete with the weight
 // stream of the resampling pass that follows.
-__device__ __forceinline__ void store_state(const Model& m, const Buffers& b, int cur, int64_t i,
-                                            const Prop& o) {
-  float* Xout = cur ? b.X0 : b.X1;
+__device__ __forceinline__ void store_state(const Model& m, const Buffers& b, int cur,
+                                            int64_t base, uint32_t t, const Prop& o) {
+  float* Xout = (cur ? b.X0 : b.X1) + base;
   const int64_t n = m.n;
-  __builtin_nontemporal_store(o.x, Xout + i);
-  __builtin_nontemporal_store(o.y, Xout + n + i);
-  __builtin_nontemporal_store(o.vx, Xout + 2 * n + i);
-  __builtin_nontemporal_store(o.vy, Xout + 3 * n + i);
-  __builtin_nontemporal_store(o.I, Xout + 4 * n + i);
+  __builtin_nontemporal_store(o.x, Xout + t);
+  __builtin_nontemporal_store(o.y, Xout + n + t);
+  __builtin_nontemporal_store(o.vx, Xout + 2 * n + t);
+  __builtin_nontemporal_store(o.vy, Xout + 3 * n + t);
+  __builtin_nontemporal_store(o.I, Xout + 4 * n + t);
 }
 
 // Fixed-point weight of a particle whose weight relative to its block
@@ -572,17 +601,17 @@ __device__ __forceinline__ double item_weight(double e) {
 __device__ __forceinline__ float exp_neg_f32(double x) {
   const double k = rint(x * 0x1.71547652b82fep+0);
   const double r = fma(-k, 0x1.62e42fefa39efp-1, x);
-  double p = 0x1.71de3a556c734p-19;     // 1/9!
-  p = fma(p, r, 0x1.a01a01a01a01ap-16);  // 1/8!
-  p = fma(p, r, 0x1.a01a01a01a01ap-13);  // 1/7!
-  p = fma(p, r, 0x1.6c16c16c16c17p-10);  // 1/6!
-  p = fma(p, r, 0x1.1111111111111p-7);   // 1/5!
-  p = fma(p, r, 0x1.5555555555555p-5);   // 1/4!
-  p = fma(p, r, 0x1.5555555555555p-3);   // 1/3!
+  double p = fma(sconst(0x1.71de3a556c734p-19), r,  // 1/9!
+                 sconst(0x1.a01a01a01a01ap-16));    // 1/8!
+  p = fma(p, r, sconst(0x1.a01a01a01a01ap-13));     // 1/7!
+  p = fma(p, r, sconst(0x1.6c16c16c16c17p-10));     // 1/6!
+  p = fma(p, r, sconst(0x1.1111111111111p-7));      // 1/5!
+  p = fma(p, r, sconst(0x1.5555555555555p-5));      // 1/4!
+  p = fma(p, r, sconst(0x1.5555555555555p-3));      // 1/3!
   p = fma(p, r, 0.5);
   p = fma(p, r, 1.0);
   p = fma(p, r, 1.0);
-  const float v = (float)ldexp(p, (int)k);
+  const float v = (float)ldexp(p, cvt_sat_i32(k));
   return x < -104.0 ? 0.0f : v;
 }
 
@@ -598,8 +627,8 @@ __device__ __forceinline__ float exp_neg_f32(double x) {
 // order-preserving integer keys so that each DPP step is one v_max_i32, and
 // within one fp32 ulp of the largest l. Where that ulp exceeds 1/8 (block
 // maxima of magnitude 2^20 and above) the exact fp64 maximum is taken instead.
-__device__ __forceinline__ double finish_block(const Buffers& b, int cur, int64_t i, bool active,
-                                               double l, const Prop& o, double* red,
+__device__ __forceinline__ double finish_block(const Buffers& b, int cur, int64_t blk,
+                                               bool active, double l, const Prop& o, double* red,
                                                double* dsh, int* ksh) {
   // lane tests compare t with wave-uniform values, so no lane index stays live
   const int t = threadIdx.x, w = wave_index(), t0 = 64 * w;
@@ -625,8 +654,8 @@ __device__ __forceinline__ double finish_block(const Buffers& b, int cur, int64_
       Ef = exp_neg_f32(l - mb);
       e = (double)Ef;
     }
-    float* Eout = cur ? b.E0 : b.E1;
-    Eout[i] = Ef;
+    float* Eout = (cur ? b.E0 : b.E1) + blk * kBlock;
+    Eout[(uint32_t)t] = Ef;
   }
   const double wi = item_weight(e);
   // after the barrier above every thread is past its reads of the LDS that
@@ -646,7 +675,7 @@ __device__ __forceinline__ double finish_block(const Buffers& b, int cur, int64_
   }
   // value 2w in row 1 of wave w, value 2w + 1 in row 3
   s = pair_rows(row_allreduce(s, OpAdd()), OpAdd(), 0.0);
-  double* R = (cur ? b.R0 : b.R1) + (i / kBlock) * kRec;
+  double* R = (cur ? b.R0 : b.R1) + blk * kRec;
   if (t == t0 + 16) R[1 + 2 * w] = s;
   if (t == t0 + 48 && 2 * w + 1 < 7) R[2 + 2 * w] = s;
   if (t == 0) R[0] = mb;
@@ -655,14 +684,17 @@ __device__ __forceinline__ double finish_block(const Buffers& b, int cur, int64_
 
 // LDS of one step workgroup: two copies of the tile of D = Z - b, each in
 // one half of the first TILE doubles of `tile` (the first 7 x 256 of them
-// double as the record exchange), then the table of row sums of D^2 (kSqCap
-// doubles); a workgroup whose box does not fit twice keeps one tile in all of
-// it. And the reduction scratch. Kernels that run several patch sizes declare
-// it once.
-template <int TILE>
+// double as the record exchange), then SQ doubles for the table of row sums of
+// D^2; a workgroup whose box does not fit twice keeps one tile in all of it.
+// And the reduction scratch. Kernels that run several patch sizes declare it
+// once. The table has an entry per tile row and centre column, fewer than a
+// copy has pixels: TILE / 2 doubles hold it (gradient mode keeps two tables in
+// kSqCap), which lets six and seven workgroups share a CU where 1536 doubles
+// let five and six.
+template <int TILE, int SQ = TILE / 2>
 struct StepLds {
   static_assert(TILE >= 7 * kBlock, "the tile doubles as the record exchange buffer");
-  __align__(16) double tile[TILE + kSqCap];
+  __align__(16) double tile[TILE + SQ];
   double dsh[4];
   int ish[16];
   int ksh[4];
@@ -859,8 +891,9 @@ __device__ __forceinline__ void patch_moments(const double* __restrict__ p0, int
 template <int P, bool GRAD = false, int TILE = kTileCap>
 __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
                                           const float* __restrict__ obs, int64_t blk,
-                                          StepLds<TILE>& L) {
+                                          StepLds<TILE, GRAD ? kSqCap : TILE / 2>& L) {
   constexpr int h = (P - 1) / 2;
+  constexpr int kSq = GRAD ? kSqCap : TILE / 2;  // doubles of the table
   double* const tile = L.tile;
   double* const sq = L.tile + TILE;
   double* const dsh = L.dsh;
@@ -870,19 +903,20 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   const double cdelta = cp->delta;
   const uint32_t k = (uint32_t)(cp->k + 1);
   const int t = threadIdx.x, w = wave_index();
-  const int64_t i = blk * kBlock + t;
-  const bool active = i < m.n;
+  const int64_t base = blk * kBlock;
+  const int rem = (int)min((int64_t)kBlock, m.n - base);  // the block's particles
+  const bool active = t < rem;
   // Lanes past the last particle (the tail of the last workgroup) repeat the
   // work of particle n - 1, which lies in the same workgroup, and store
   // nothing: every lane runs the same instructions on valid data.
-  const int64_t ia = active ? i : m.n - 1;
+  const int ta = min(t, rem - 1);
 
   Prop o;
   float tg[kNTan];  // gradient mode: the particle's new tangents
   if constexpr (GRAD) {
     float z[5];
     int64_t p;
-    o = propagate(m, b, cur, mode, ia, k, z, &p);
+    o = propagate(m, b, cur, mode, base, ta, k, z, &p);
     // tangents along the ancestral line (see kNTan): dx'/dq_x = dx/dq_x +
     // z_x, dx'/dq_vx = dx/dq_vx + dvx/dq_vx (the parent's), and alike
     const float* Tin = cur ? b.T1 : b.T0;
@@ -899,11 +933,12 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
     tg[6] = (float)((double)tp[6] + (double)z[4]);
     if (active)  // streamed like the states
 #pragma unroll
-      for (int d = 0; d < kNTan; ++d) __builtin_nontemporal_store(tg[d], Tout + (int64_t)d * m.n + i);
+      for (int d = 0; d < kNTan; ++d)
+        __builtin_nontemporal_store(tg[d], Tout + (int64_t)d * m.n + base + (uint32_t)t);
   } else {
-    o = propagate(m, b, cur, mode, ia, k);
+    o = propagate(m, b, cur, mode, base, ta, k);
   }
-  if (active) store_state(m, b, cur, i, o);
+  if (active) store_state(m, b, cur, base, t, o);
   // patch centre: pixel nearest to (x, y); the offset f is exact in fp64
   const double rx = floor((double)o.x + 0.5);
   const double ry = floor((double)o.y + 0.5);
@@ -911,9 +946,10 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   const double fy = (double)o.y - ry;
   // addresses only: far-away centres are clamped to [-P, W + P] x [-P, H + P],
   // where the whole patch already lies outside the frame (its pixels read as
-  // background); a NaN centre goes to the low corner
-  const int cx = (int)fmin(fmax(rx, m.clo[0]), m.chi[0]);
-  const int cy = (int)fmin(fmax(ry, m.clo[1]), m.chi[1]);
+  // background); a NaN centre reads as 0 (its weight is NaN: the step is rolled
+  // back)
+  const int cx = min(max(cvt_sat_i32(rx), -P), m.W + P);
+  const int cy = min(max(cvt_sat_i32(ry), -P), m.H + P);
   // The 1-D Gaussian factors of Eq. 3 at the patch's pixel offsets. Only
   // their products g_x g_y enter the likelihood, so g_x is taken relative to
   // its first value, which moves into the first g_y: three exps per particle
@@ -921,7 +957,7 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   // normal).
   double gx[P];
   gx[0] = 1.0;
-  const double bx = exp_fast(2.0 * fx * m.inv2s2);
+  const double bx = exp_fast(fx * m.is2);
 #pragma unroll
   for (int d = 0; d + 1 < P; ++d) gx[d + 1] = gx[d] * (m.gstep[d] * bx);
   double G2x = 0.0;
@@ -929,25 +965,18 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   for (int d = 0; d < P; ++d) G2x = fma(gx[d], gx[d], G2x);
   const double ax = (double)h + fx, ay = (double)h + fy;
   const double gy0 = exp_fast(-(ax * ax + ay * ay) * m.inv2s2);
-  const double by = exp_fast(2.0 * fy * m.inv2s2);
+  const double by = exp_fast(fy * m.is2);
   // Bounding box of the workgroup's patch centres (the tail lanes repeat
-  // particle n - 1, whose centre is in the box anyway). Each lane packs the
-  // offsets (ox, oy) of its centre from lane 0's, saturated to +-32767, as
-  // two int16 (for the minima) and their negations (for the maxima); an
-  // offset at the saturation bound already makes the box wider than any
-  // tile, so the saturated box still selects the global path.
+  // particle n - 1, whose centre is in the box anyway): four reductions whose
+  // every step is one instruction with its lane move.
   {
-    const int bx0 = readlane(cx, 0), by0 = readlane(cy, 0);
-    const int ox = min(max(cx - bx0, -32767), 32767), oy = min(max(cy - by0, -32767), 32767);
-    const uint32_t pmin = (uint32_t)(uint16_t)ox | ((uint32_t)(uint16_t)oy << 16);
-    const uint32_t pneg = (uint32_t)(uint16_t)-ox | ((uint32_t)(uint16_t)-oy << 16);
-    const uint32_t rmin = wave_reduce_last(pmin, OpMin16x2(), 0x7fff7fffu);
-    const uint32_t rneg = wave_reduce_last(pneg, OpMin16x2(), 0x7fff7fffu);
+    const int x0 = wave_reduce_last(cx, OpMin(), INT_MAX), x1 = wave_reduce_last(cx, OpMax(), INT_MIN);
+    const int y0 = wave_reduce_last(cy, OpMin(), INT_MAX), y1 = wave_reduce_last(cy, OpMax(), INT_MIN);
     if (t == 64 * w + 63) {
-      ish[w] = bx0 + (int16_t)(rmin & 0xffffu);
-      ish[4 + w] = bx0 - (int16_t)(rneg & 0xffffu);
-      ish[8 + w] = by0 + (int16_t)(rmin >> 16);
-      ish[12 + w] = by0 - (int16_t)(rneg >> 16);
+      ish[w] = x0;
+      ish[4 + w] = x1;
+      ish[8 + w] = y0;
+      ish[12 + w] = y1;
     }
   }
   __syncthreads();
@@ -975,7 +1004,7 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   const int tx0 = mnx - h, ty0 = mny - h;
   const int64_t acx = (int64_t)mxx - mnx + 1;
   const int64_t nH = th64 * acx;
-  const bool use_tab = use_lds && nH <= kSqCap;
+  const bool use_tab = use_lds && nH <= kSq;  // (the plain step's always fits)
   // gradient mode also tables the row sums of D, in the upper half, when both
   // fit (the D^2 table is used exactly when the plain step uses it, so the log
   // weights stay the plain step's)
@@ -1021,7 +1050,7 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   // from a Gaussian prior 278 -> 67 us; a step of 2^20 particles that lost the
   // spot (9 x 9) 44.5 -> 34.7 us. Gradient mode keeps the two choices: a third
   // cost its kernel 2 % (registers) on clouds that never need it.
-  constexpr int kAll = TILE + kSqCap;
+  constexpr int kAll = TILE + kSq;
   enum { kFrame, kFloat, kDouble };
   int single = kFrame;  // uniform in a wave
   int sx0 = tx0, sy0 = ty0, sw = 0, sbase = 0;
@@ -1091,7 +1120,6 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   // every lane's patch lies in the tile (the tail lanes' is particle
   // n - 1's); finish_block ignores the tail lanes' l
   double l;
-  int64_t il = i;  // the particle index where the record is written
   double gth[GRAD ? kNGrad : 1] = {};
   // the particle's first patch row in copy A (even first column) or B (odd)
   const int col0 = cx - h - tx0;
@@ -1102,7 +1130,7 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
     // frame row of the patch's first row; centres far outside are clamped,
     // as for the addresses (every row of such a patch is outside the frame)
     const int64_t v0 = (int64_t)fmin(fmax(ry, -(double)P - 1.0), (double)m.H + P + 1.0) - h;
-    // table index of the centre (below nH <= kSqCap where a table is used)
+    // table index of the centre (below nH where a table is used)
     const int at = use_tab ? (cy - mny) * (int)acx + (cx - mnx) : 0;
     if (use_sum) {
       patch_moments<P, true, true, false>(p0, ts, sq + at, sq + kTab + at, (int)acx, obs, 0,
@@ -1119,7 +1147,7 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
     }
     const double I = (double)o.I;
     const double ssq = mo.sd2 - 2.0 * I * mo.X0 + I * I * (G2x * mo.B0);
-    l = prior_lw(m, b, cur, mode, cdelta, amv, ia) - ssq * m.inv2sig2 - m.lognorm_obs;
+    l = prior_lw(m, b, cur, mode, cdelta, amv, base + ta) - ssq * m.inv2sig2 - m.lognorm_obs;
     // 1-D moments of g_x^2 and the in-frame sum of g_x (true centre rx)
     double A1 = 0.0, A2 = 0.0, Gin_x = 0.0;
 #pragma unroll
@@ -1157,7 +1185,7 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   } else {
     double X = 0.0, G2y = 0.0, sd2 = 0.0;
     if (use_tab) {
-      // the table index is below nH <= kSqCap: 32-bit arithmetic
+      // the table index is below nH <= kSq: 32-bit arithmetic
       patch_lds<P, true>(p0, ts, sq + ((cy - mny) * (int)acx + (cx - mnx)), (int)acx, gx, gy0,
                          by, m.gstep, X, G2y, sd2);
     } else if (use_lds) {
@@ -1172,20 +1200,11 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
     } else {
       patch_global<P>(obs, cx - h, cy - h, m.W, m.H, m.b, gx, gy0, by, m.gstep, X, G2y, sd2);
     }
-    if constexpr (TILE < kTileCap) {
-      // the six-wave shape: the particle index again, from a fresh copy of
-      // the thread index, instead of two registers held across the patch
-      // sums (they made 13 x 13 spill there)
-      int tl = t;
-      asm volatile("" : "+v"(tl));
-      il = blk * kBlock + tl;
-    }
-    const int64_t ial = il < m.n ? il : m.n - 1;
     const double I = (double)o.I;
     const double ssq = sd2 - 2.0 * I * X + I * I * (G2x * G2y);
-    l = prior_lw(m, b, cur, mode, cdelta, amv, ial) - ssq * m.inv2sig2 - m.lognorm_obs;
+    l = prior_lw(m, b, cur, mode, cdelta, amv, base + ta) - ssq * m.inv2sig2 - m.lognorm_obs;
   }
-  const double e = finish_block(b, cur, il, active, l, o, tile, dsh, L.ksh);
+  const double e = finish_block(b, cur, blk, active, l, o, tile, dsh, L.ksh);
   if constexpr (GRAD) {
     // the block's sum_i E_i d l_i / d theta, weighted like the MMSE sums and
     // reduced the same way: derivatives 0-7 through the tile, 8 through the
@@ -1220,9 +1239,7 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
 }
 
 // Patches up to 13 x 13 come in two workgroup shapes: five waves per SIMD, or
-// six with a smaller tile (13 x 13 fits six waves' registers without spilling
-// because step_spot recomputes the particle index after the patch sums);
-// wider patches keep the compiler's default budget.
+// six with a smaller tile; wider patches keep the compiler's default budget.
 template <int P, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kShapeWaves[S])))
 void k_step_spot(Model m, Buffers b, const float* __restrict__ obs) {
@@ -1241,7 +1258,7 @@ __global__ __launch_bounds__(256) void k_step_spot_wide(Model m, Buffers b,
 template <int P>
 __global__ __launch_bounds__(256) void k_step_spot_grad(Model m, Buffers b,
                                                         const float* __restrict__ obs) {
-  __shared__ StepLds<kTileCap> L;
+  __shared__ StepLds<kTileCap, kSqCap> L;
   step_spot<P, true>(m, b, obs, blockIdx.x, L);
 }
 
@@ -1255,19 +1272,19 @@ __global__ __launch_bounds__(256) void k_step_lg(Model m, Buffers b,
   const int cur = cp->cur, mode = cp->mode, amv = cp->arna_moved;
   const double cdelta = cp->delta;
   const uint32_t k = (uint32_t)(cp->k + 1);
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.x * kBlock, i = base + threadIdx.x;
   const bool active = i < m.n;
   Prop o{};
   double l = -INFINITY;
   if (active) {
-    o = propagate(m, b, cur, mode, i, k);
-    store_state(m, b, cur, i, o);
+    o = propagate(m, b, cur, mode, base, threadIdx.x, k);
+    store_state(m, b, cur, base, threadIdx.x, o);
     const double ex = (double)obs[0] - (double)o.x, ey = (double)obs[1] - (double)o.y,
                  eI = (double)obs[2] - (double)o.I;
     l = prior_lw(m, b, cur, mode, cdelta, amv, i) - ex * ex * m.lg_inv2r2[0] - ey * ey * m.lg_inv2r2[1] - eI * eI * m.lg_inv2r2[2] -
         m.lg_norm;
   }
-  finish_block(b, cur, i, active, l, o, red, dsh, ksh);
+  finish_block(b, cur, blockIdx.x, active, l, o, red, dsh, ksh);
 }
 
 // Records of caller-supplied absolute fp32 log weights (standalone

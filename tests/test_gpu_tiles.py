@@ -19,7 +19,7 @@ torch = pytest.importorskip("torch")
 
 W, H = 230, 200
 # doubles of LDS a workgroup of each shape (and wider patches) keeps its tile in
-ALL = {0: 3584, 1: 3328}
+ALL = {0: 3072, 1: 2688}
 
 
 @pytest.fixture(scope="module")
