@@ -3296,6 +3296,32 @@ __global__ __launch_bounds__(256) void k_dlb_entries(int32_t kind, const int32_t
 // track, one workgroup per work item (track, index of the track's block,
 // chunk, segment or group) from a list built on the host, with the track's
 // model and buffers read from device arrays.
+// A pointer that was read from memory, as one to global memory (which it is):
+// the compiler otherwise has to use flat accesses, which also occupy the LDS path
+// and wait on its counter.
+template <class T>
+__device__ __forceinline__ T* as_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)reinterpret_cast<uintptr_t>(p);
+}
+__device__ __forceinline__ Buffers track_buffers(const Buffers& s) {
+  Buffers b = s;
+  b.ctrl = as_global(s.ctrl);
+  b.X0 = as_global(s.X0);
+  b.X1 = as_global(s.X1);
+  b.E0 = as_global(s.E0);
+  b.E1 = as_global(s.E1);
+  b.R0 = as_global(s.R0);
+  b.R1 = as_global(s.R1);
+  b.pfx = as_global(s.pfx);
+  b.CR = as_global(s.CR);
+  b.cpre = as_global(s.cpre);
+  b.anc = as_global(s.anc);
+  b.lw64 = as_global(s.lw64);
+  b.lwg = as_global(s.lwg);
+  b.hq = as_global(s.hq);
+  return b;
+}
+
 __device__ __forceinline__ WeightSrc own_weights(const Buffers& b) {
   WeightSrc w{};
   w.E0 = b.E0;
@@ -3311,7 +3337,7 @@ __global__ __launch_bounds__(256) void k_init_batch(const Model* __restrict__ ms
                                                     const Buffers* __restrict__ bs,
                                                     const BatchItem* __restrict__ items) {
   const BatchItem it = items[blockIdx.x];
-  init_body(ms[it.track], bs[it.track], it.idx);
+  init_body(ms[it.track], track_buffers(bs[it.track]), it.idx);
 }
 
 template <int P>
@@ -3321,7 +3347,7 @@ __global__ __launch_bounds__(256) void k_step_batch_wide(const Model* __restrict
                                                          const float* __restrict__ obs) {
   __shared__ StepLds<kTileCap> L;
   const BatchItem it = items[blockIdx.x];
-  step_spot<P>(ms[it.track], bs[it.track], obs, it.idx, L);
+  step_spot<P>(ms[it.track], track_buffers(bs[it.track]), obs, it.idx, L);
 }
 
 // Every patch size up to kFusedMaxP in one launch of workgroup shape S: each
@@ -3335,7 +3361,7 @@ void k_step_batch_fused(const Model* __restrict__ ms, const Buffers* __restrict_
   __shared__ StepLds<T> L;
   const BatchItem it = items[blockIdx.x];
   const Model& m = ms[it.track];
-  const Buffers& b = bs[it.track];
+  const Buffers b = track_buffers(bs[it.track]);
   switch (m.P) {
     case 1: step_spot<1, false, T>(m, b, obs, it.idx, L); break;
     case 3: step_spot<3, false, T>(m, b, obs, it.idx, L); break;
@@ -3353,20 +3379,20 @@ __global__ __launch_bounds__(256) void k_merge_batch(const Model* __restrict__ m
                                                      const Buffers* __restrict__ bs,
                                                      const BatchItem* __restrict__ items) {
   const BatchItem it = items[blockIdx.x];
-  merge_chunk(ms[it.track], bs[it.track], 0, it.idx);
+  merge_chunk(ms[it.track], track_buffers(bs[it.track]), 0, it.idx);
 }
 
 // One workgroup per track.
 __global__ __launch_bounds__(256) void k_merge_final_batch(const Model* __restrict__ ms,
                                                            const Buffers* __restrict__ bs) {
-  merge_final<4>(ms[blockIdx.x], bs[blockIdx.x], 0, 0.0);
+  merge_final<4>(ms[blockIdx.x], track_buffers(bs[blockIdx.x]), 0, 0.0);
 }
 
 __global__ __launch_bounds__(kWave) void k_anc_batch(const Model* __restrict__ ms,
                                                    const Buffers* __restrict__ bs,
                                                    const BatchItem* __restrict__ items) {
   const BatchItem it = items[blockIdx.x];
-  const Buffers& b = bs[it.track];
+  const Buffers b = track_buffers(bs[it.track]);
   anc_seg<false>(ms[it.track], b, own_weights(b), it.idx);
 }
 
@@ -3396,7 +3422,7 @@ __global__ __launch_bounds__(kWave) void k_fill_batch(const Model* __restrict__ 
       cnt[u] = 0;
       if (tr[u] >= 0) {
         const Buffers& b = bs[tr[u]];
-        const Ctrl* c = b.ctrl;
+        const Ctrl* c = as_global(b.ctrl);
         if (c->do_resample) cnt[u] = (int)max((int64_t)0, min((int64_t)c->heavy_count, b.hq_cap));
       }
     }
@@ -3414,7 +3440,7 @@ __global__ __launch_bounds__(kWave) void k_fill_batch(const Model* __restrict__ 
         const int owner = __popcll(__ballot(incl <= r));
         const int32_t t_own = readlane(tr[u], owner);
         const int first = readlane(incl - cnt[u], owner);
-        const Buffers& b = bs[t_own];
+        const Buffers b = track_buffers(bs[t_own]);
         fill_entry<false>(ms[t_own], b, own_weights(b), res_in(b.ctrl), r - first);
       }
       base += tot;
@@ -3426,7 +3452,7 @@ __global__ __launch_bounds__(256) void k_rna_batch(const Model* __restrict__ ms,
                                                    const Buffers* __restrict__ bs,
                                                    const BatchItem* __restrict__ items) {
   const BatchItem it = items[blockIdx.x];
-  const Buffers& b = bs[it.track];
+  const Buffers b = track_buffers(bs[it.track]);
   // (a work item per group, whatever its size: one group to a workgroup)
   rna_body<4>(ms[it.track], b, own_weights(b), nullptr, it.idx);
 }
