@@ -178,7 +178,7 @@ int64_t record_blocks(int64_t n) { return (n + ppf::kBlock - 1) / ppf::kBlock; }
 int64_t merge_chunk(int64_t nb) {
   int64_t per = (nb + 256 * 256 - 1) / (256 * 256);
   if (per < 1) per = 1;
-  if (per > 8) per = 8;
+  if (per > ppf::kMergePer) per = ppf::kMergePer;
   return 256 * per;
 }
 int64_t seg_count(int64_t n) { return (n + ppf::kSegItems - 1) / ppf::kSegItems; }
@@ -1005,6 +1005,7 @@ struct BatchPlan {
   std::vector<Buffers> bufs;
   std::vector<ppf::BatchItem> blocks, chunks, segs, groups;
   std::vector<int32_t> sys_tracks;
+  int64_t most_chunks = 0;  // of a track
   struct StepRange {
     int P;      // patch size; 0: sizes up to kFusedMaxP in one fused launch
     int shape;  // workgroup shape of a fused launch
@@ -1089,6 +1090,7 @@ void plan_batch(const ppf_params* p, int32_t count, BatchPlan* bp) {
   order_steps(bp, bp->shape_of);
   for (int32_t t = 0; t < count; ++t) {
     for (int64_t j = 0; j < bp->bufs[t].nch; ++j) bp->chunks.push_back({t, (int32_t)j});
+    bp->most_chunks = std::max(bp->most_chunks, bp->bufs[t].nch);
     if (p[t].resample == PPF_RESAMPLE_RNA) {
       for (int64_t g = 0; g < bp->models[t].G; ++g) bp->groups.push_back({t, (int32_t)g});
     } else {
@@ -1255,7 +1257,8 @@ int enqueue_batch_step(ppf_batch h, const float* obs_dev) {
   if (rc0) return rc0;
   int rc = h->run(kKMerge, [&] {
     return ppf::launch_merge_batch(h->d_models, h->d_bufs, h->d_chunks,
-                                   (int64_t)bp.chunks.size(), h->count, h->stream);
+                                   (int64_t)bp.chunks.size(), h->count, bp.most_chunks,
+                                   h->stream);
   });
   if (rc) return rc;
   if (!bp.segs.empty()) {

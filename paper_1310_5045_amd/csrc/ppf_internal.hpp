@@ -47,6 +47,7 @@ constexpr double kItemToCdf = 0x1p18;
 // would take them in turns on one CU: about 2 us of vector work for every four
 // chunks, against one more launch.
 constexpr int kOneMergeChunks = 4;
+constexpr int kMergePer = 8;  // a merge chunk is at most 256 kMergePer records
 
 // Systematic resampling: one wave per segment of kSegBlocks blocks writes the
 // segment's output slots itself when they span at most kCoopTiles tiles of
@@ -300,9 +301,10 @@ hipError_t launch_step_batch(int P, const Model* ms, const Buffers* bs, const Ba
 hipError_t launch_step_batch_fused(int shape, const Model* ms, const Buffers* bs,
                                    const BatchItem* items, int64_t n_items, const float* obs,
                                    hipStream_t s);
-// The chunk merges (items), then one final merge per track.
+// The chunk merges (items), then one final merge per track; or both in one launch.
+// most: the most chunks that a track has.
 hipError_t launch_merge_batch(const Model* ms, const Buffers* bs, const BatchItem* items,
-                              int64_t n_items, int32_t n_tracks, hipStream_t s);
+                              int64_t n_items, int32_t n_tracks, int64_t most, hipStream_t s);
 hipError_t launch_anc_batch(const Model* ms, const Buffers* bs, const BatchItem* items,
                             int64_t n_items, hipStream_t s);
 hipError_t launch_fill_batch(const Model* ms, const Buffers* bs, const int32_t* tracks,

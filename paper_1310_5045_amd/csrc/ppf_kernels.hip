@@ -1375,7 +1375,7 @@ __global__ __launch_bounds__(256) void k_records(Model m, Buffers b,
 // division for the five means). With at most kOneMergeChunks chunks of 256
 // records one launch does both, the chunks side by side in one workgroup and
 // their records in LDS: 4096 particles 3.5 + 4.9 us in two launches, 5.5 us in
-// one; 100,003 3.9 + 4.8 and 6.0 us; 262,144 with derivatives 5.4 + 6.8 and 11.0
+// one; 100,003 3.9 + 4.8 and 5.7 us; 262,144 with derivatives 5.4 + 6.8 and 9.1
 // us (a gap between two launches is another 1 us or so).
 struct MergeSh {
   double mx[4];
@@ -1440,7 +1440,7 @@ __device__ __forceinline__ void merge_chunk_body(const Model& m, const Buffers& 
   const int64_t lo = ch * b.chunk, hi = min(b.nb, lo + b.chunk);
   const int per = ONE ? 1 : (int)(b.chunk / 256);
   const int64_t j0 = lo + (int64_t)t * per;
-  constexpr int kPer = ONE ? 1 : 8;  // records per thread at most
+  constexpr int kPer = ONE ? 1 : kMergePer;  // records per thread at most
 
   double rec[kRec], rec1[kRec];  // ONE: the thread's record, from either buffer
   if (ONE) {
@@ -1511,12 +1511,103 @@ __device__ __forceinline__ void merge_chunk_body(const Model& m, const Buffers& 
   }
 }
 
+// With derivatives, by columns: lane d of a row of 16 takes sum d of kSums (sum E^2,
+// sum E x, the derivatives) and the rows take the records in turn, so that a wave reads
+// whole records and ends with two exchanges between its rows. A thread to a record
+// needs six exchanges for each of the 15 sums, 270 fp64 steps a wave instead of 20, and
+// its loads touch a line per lane: 262,144 particles in four chunks 10.8 -> 9.1 us.
+// Without derivatives the wait for the factors costs more than that saves (two chunks
+// 5.7 -> 6.1 us, and 7.5 with the columns of both buffers loaded ahead), so those keep
+// a thread to a record.
+constexpr int kSums = 6 + kNGrad;
+static_assert(kSums <= 16 && kRec == 8, "a lane of a row per sum");
+struct SumColumn {
+  const double* p;  // the column's value in record 0
+  int stride;
+  bool grad;
+  __device__ __forceinline__ SumColumn(const double* R, const double* RG, int d) {
+    grad = d >= 6 && d < kSums;
+    p = grad ? RG + (d - 6) : R + (d < 6 ? 2 + d : 0);  // (lanes past the sums: unused)
+    stride = grad ? kNGrad : kRec;
+  }
+};
+
+// Sum over the wave's four rows of 16 lanes, lane by lane.
+__device__ __forceinline__ double sum_of_rows(double v) {
+  typedef uint32_t U2 __attribute__((ext_vector_type(2)));
+  auto pair = [](U2 lo, U2 hi) {
+    auto d = [](uint32_t l, uint32_t h) {
+      return __longlong_as_double((long long)(((uint64_t)h << 32) | l));
+    };
+    return d(lo.x, hi.x) + d(lo.y, hi.y);
+  };
+  uint64_t x = (uint64_t)__double_as_longlong(v);
+  uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+  v = pair(__builtin_amdgcn_permlane16_swap(lo, lo, false, false),
+           __builtin_amdgcn_permlane16_swap(hi, hi, false, false));
+  x = (uint64_t)__double_as_longlong(v);
+  lo = (uint32_t)x;
+  hi = (uint32_t)(x >> 32);
+  return pair(__builtin_amdgcn_permlane32_swap(lo, lo, false, false),
+              __builtin_amdgcn_permlane32_swap(hi, hi, false, false));
+}
+
+// The same for a chunk of 256 records with derivatives, by columns. fac: LDS for the
+// records' factors, part: for its waves' sums.
+__device__ __forceinline__ void merge_chunk_deriv(const Model& m, const Buffers& b, int ch,
+                                                  int t, int w, MergeSh& sh, double* fac,
+                                                  double* part, double* cr, double* crg) {
+  const int64_t lo = ch * 256, hi = min(b.nb, lo + 256), j = lo + t;
+  const int64_t jr = min(j, b.nb - 1) * kRec;
+  double rm = b.R0[jr], rq = b.R0[jr + 1];  // the thread's record, from either buffer
+  const double rm1 = b.R1[jr], rq1 = b.R1[jr + 1];
+  const int which = b.ctrl->cur ^ 1;  // the records this step wrote
+  const double* R = which ? b.R1 : b.R0;
+  const int d = t & 15, row = t >> 4;
+  const SumColumn col(R, b.RG, d);
+  double x[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) x[q] = col.p[min(lo + q * 16 + row, hi - 1) * col.stride];
+  if (which) {
+    rm = rm1;
+    rq = rq1;
+  }
+  const double Mc = group_reduce<4>(j < hi ? rm : -INFINITY, sh.mx, w, OpMax());
+  const double f = (j < hi && rm != -INFINITY) ? exp(rm - Mc) : 0.0;
+  const uint64_t qj = j < hi ? (uint64_t)rint(rq * f) : 0;
+  fac[t] = f;
+  uint64_t qtot;
+  const uint64_t run = group_excl_sum<4>(qj, sh.q, w, &qtot);  // (its barrier covers fac)
+  if (j < hi) b.pfx[j] = run;
+  double acc = 0.0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const double fe = fac[q * 16 + row];
+    const double y = x[q] * (d == 0 ? fe * fe : fe);
+    acc += (col.grad && fe == 0.0) ? 0.0 : y;
+  }
+  acc = sum_of_rows(acc);
+  if ((t & 63) < 16) part[w * 16 + d] = acc;
+  __syncthreads();
+  if (t < 16) {
+    const double v = (part[t] + part[16 + t]) + (part[32 + t] + part[48 + t]);
+    if (t < 6) cr[2 + t] = v;
+    if (col.grad) crg[t - 6] = v;
+    if (t == 0) {
+      cr[0] = Mc;
+      cr[1] = __longlong_as_double((long long)qtot);
+    }
+  }
+}
+
 // By one workgroup of WAVES waves holding the chunks (at most 64 with one
-// wave); CR, CRG: the chunk records, in global memory or in LDS.
-template <int WAVES>
+// wave); CR, CRG: the chunk records, in global memory or in LDS. BYCOL: one wave and
+// up to kOneMergeChunks chunks, their sums by columns; fac: LDS for their factors.
+template <int WAVES, bool BYCOL = false>
 __device__ __forceinline__ void merge_final_body(const Model& m, const Buffers& b, int standalone,
                                                  double u_given, const double* CR,
-                                                 const double* CRG, MergeSh& sh) {
+                                                 const double* CRG, MergeSh& sh,
+                                                 double* fac = nullptr) {
   __shared__ uint64_t ush[4];
   Ctrl* c = b.ctrl;
   const int t = threadIdx.x, w = WAVES == 1 ? 0 : wave_index();
@@ -1554,6 +1645,10 @@ __device__ __forceinline__ void merge_final_body(const Model& m, const Buffers& 
       const double f = (mc == -INFINITY) ? 0.0 : exp(mc - M);
       const uint64_t Q = (uint64_t)__double_as_longlong(field(cc, 1));
       tot7[0] += (double)Q * f;
+      if (BYCOL) {
+        fac[t] = (mc == -INFINITY) ? -1.0 : f;  // (-1: no weight, whatever the derivatives)
+        continue;
+      }
       tot7[1] += field(cc, 2) * (f * f);
 #pragma unroll
       for (int d = 0; d < 5; ++d) tot7[2 + d] += field(cc, 3 + d) * f;
@@ -1562,9 +1657,31 @@ __device__ __forceinline__ void merge_final_body(const Model& m, const Buffers& 
         for (int d = 0; d < kNGrad; ++d) G[d] += CRG[cc * kNGrad + d] * f;
     }
   }
-  group_sum_n<WAVES>(tot7, sh.sums, w);
+  if (BYCOL) {
+    double s1[1] = {tot7[0]};
+    group_sum_n<1>(s1, nullptr, w);
+    tot7[0] = s1[0];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    static_assert(kOneMergeChunks == 4, "a chunk per row");
+    const SumColumn col(CR, CRG, t & 15);
+    const int cc = t >> 4;
+    double acc = 0.0;
+    if (cc < nch) {
+      const double f = fac[cc], g = fmax(f, 0.0);
+      const double y = col.p[cc * col.stride] * ((t & 15) == 0 ? g * g : g);
+      acc = (col.grad && f < 0.0) ? 0.0 : y;
+    }
+    acc = sum_of_rows(acc);
+#pragma unroll
+    for (int d = 0; d < 6; ++d) tot7[1 + d] = readlane(acc, d);
+#pragma unroll
+    for (int d = 0; d < kNGrad; ++d) G[d] = readlane(acc, 6 + d);
+  } else {
+    group_sum_n<WAVES>(tot7, sh.sums, w);
+    if (m.grad) group_sum_n<WAVES, kNGrad>(G, sh.grads, w);
+  }
   const double S = tot7[0] * (1.0 / kItemScale), S2 = tot7[1];
-  if (m.grad) group_sum_n<WAVES, kNGrad>(G, sh.grads, w);
 
   // every thread takes the step's scalars
   bool ok = isfinite(M) && isfinite(S) && S > 0.0 && isfinite(S2);
@@ -1689,17 +1806,33 @@ __global__ __launch_bounds__(64 * WAVES) void k_merge_final(Model m, Buffers b, 
 
 // Both, for at most kOneMergeChunks chunks of 256 records: 256 threads to a
 // chunk, then the first wave (the others would only take issue slots from it).
+// GRAD: the filter has derivatives.
+template <bool GRAD>
+__device__ __forceinline__ void merge_one(const Model& m, const Buffers& b, int standalone,
+                                          double u_given) {
+  __shared__ MergeSh sh[kOneMergeChunks];
+  __shared__ double cr[kOneMergeChunks * kRec], crg[kOneMergeChunks * kNGrad];
+  const int sub = wave_index() >> 2, t = threadIdx.x & 255, w = wave_index() & 3;
+  if constexpr (GRAD) {
+    __shared__ double fac[256 * kOneMergeChunks], part[64 * kOneMergeChunks];
+    merge_chunk_deriv(m, b, sub, t, w, sh[sub], fac + 256 * sub, part + 64 * sub,
+                      cr + sub * kRec, crg + sub * kNGrad);
+    __syncthreads();
+    if (wave_index() != 0) return;
+    merge_final_body<1, true>(m, b, standalone, u_given, cr, crg, sh[0], fac);
+  } else {
+    merge_chunk_body<true>(m, b, standalone, sub, t, w, sh[sub], cr + sub * kRec,
+                           crg + sub * kNGrad);
+    __syncthreads();
+    if (wave_index() != 0) return;
+    merge_final_body<1>(m, b, standalone, u_given, cr, crg, sh[0]);
+  }
+}
+template <bool GRAD>
 __global__ __launch_bounds__(256 * kOneMergeChunks) void k_merge_one(Model m, Buffers b,
                                                                      int standalone,
                                                                      double u_given) {
-  __shared__ MergeSh sh[kOneMergeChunks];
-  __shared__ double cr[kOneMergeChunks * kRec], crg[kOneMergeChunks * kNGrad];
-  const int sub = wave_index() >> 2;
-  merge_chunk_body<true>(m, b, standalone, sub, threadIdx.x & 255, wave_index() & 3, sh[sub],
-                         cr + sub * kRec, crg + sub * kNGrad);
-  __syncthreads();
-  if (wave_index() != 0) return;
-  merge_final_body<1>(m, b, standalone, u_given, cr, crg, sh[0]);
+  merge_one<GRAD>(m, b, standalone, u_given);
 }
 
 // --------------------------------------------------- systematic resampling
@@ -3385,7 +3518,12 @@ __global__ __launch_bounds__(256) void k_merge_batch(const Model* __restrict__ m
   merge_chunk(ms[it.track], track_buffers(bs[it.track]), 0, it.idx);
 }
 
-// One workgroup per track.
+// One workgroup per track. (256 tracks of 46 K particles: 8.8 us, and 5.2 + 5.9 and the
+// gap between them in two launches.)
+__global__ __launch_bounds__(256 * kOneMergeChunks) void k_merge_one_batch(
+    const Model* __restrict__ ms, const Buffers* __restrict__ bs) {
+  merge_one<false>(ms[blockIdx.x], track_buffers(bs[blockIdx.x]), 0, 0.0);
+}
 __global__ __launch_bounds__(256) void k_merge_final_batch(const Model* __restrict__ ms,
                                                            const Buffers* __restrict__ bs) {
   merge_final<4>(ms[blockIdx.x], track_buffers(bs[blockIdx.x]), 0, 0.0);
@@ -3784,8 +3922,11 @@ hipError_t launch_step_batch(int P, const Model* ms, const Buffers* bs, const Ba
 }
 
 hipError_t launch_merge_batch(const Model* ms, const Buffers* bs, const BatchItem* items,
-                              int64_t n_items, int32_t n_tracks, hipStream_t s) {
+                              int64_t n_items, int32_t n_tracks, int64_t most, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
+  if (most <= kOneMergeChunks)
+    return launch_k(k_merge_one_batch, dim3((unsigned)n_tracks), dim3(256 * (unsigned)most), s, ms,
+                    bs);
   const hipError_t e = launch_k(k_merge_batch, dim3((unsigned)n_items), dim3(256), s, ms, bs,
                                 items);
   if (e != hipSuccess) return e;
@@ -3942,8 +4083,8 @@ hipError_t launch_dlb_schedule(int32_t kind, const int32_t* counts, int32_t G, i
 hipError_t launch_merge(const Model& m, const Buffers& b, int standalone, double u_given,
                         hipStream_t s) {
   if (b.nch <= kOneMergeChunks && b.chunk == 256)
-    return launch_k(k_merge_one, dim3(1), dim3(256 * (unsigned)b.nch), s, m, b, standalone,
-                    u_given);
+    return launch_k(m.grad ? k_merge_one<true> : k_merge_one<false>, dim3(1),
+                    dim3(256 * (unsigned)b.nch), s, m, b, standalone, u_given);
   const hipError_t e = launch_k(k_merge, dim3((unsigned)b.nch), dim3(256), s, m, b, standalone);
   if (e != hipSuccess) return e;
   if (b.nch <= 64) return launch_k(k_merge_final<1>, dim3(1), dim3(64), s, m, b, standalone, u_given);
