@@ -290,10 +290,10 @@ int ppf_set_graph(ppf_handle h, int enable);
  *   0  LDS image tile of up to 2048 doubles, compiled for 5 waves per SIMD
  *   1  tile of up to 1792 doubles, 6 waves per SIMD (six workgroups share a
  *      CU, fewer registers per lane)
- * Both compute the same likelihood; a workgroup whose patches span between
- * 1792 and 2048 tile pixels reads them from the frame under shape 1 instead
- * of from LDS, which sums the same terms in another order. Create selects
- * shape 0.
+ * Both compute the same likelihood. The tile holds two copies of the pixels
+ * that a workgroup's patches span; a workgroup whose pixels fit twice in 2048
+ * doubles but not in 1792 takes its sums in another order under shape 1 (that of
+ * a box kept once, or of the frame). Create selects shape 0.
  */
 #define PPF_NUM_SHAPES 2
 /* Most tuning candidates any autotune call times (size of its ms_out). */

@@ -25,7 +25,7 @@ using ppf::Model;
 namespace {
 
 // Timed units of a step. k_resample is the systematic resampling pass, its
-// two launches (segments, then queued tile chunks) under one pair of events.
+// one or two launches (segments, then queued tile chunks) under one pair of events.
 enum KernelId {
   kKStep, kKMerge, kKResample, kKRna, kKInit, kKGather, kKLogw, kKRpa, kNumKernels
 };

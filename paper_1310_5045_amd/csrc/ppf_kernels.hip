@@ -1,6 +1,6 @@
 // HIP kernels of the SIR filter step for gfx950 (CDNA4, wave64).
 //
-// One step of Algorithm 1 (Section 2) is four or five launches on one
+// One step of Algorithm 1 (Section 2) is three to five launches on one
 // stream, with every decision taken on the device (so the same sequence
 // serves every step, and a HIP graph of it can be replayed):
 //   k_step         gather parent + propagate (Section 6.1) + patch likelihood
@@ -9,11 +9,13 @@
 //   k_merge_final  fixed-order merge of the chunks: the normaliser, ESS, MMSE
 //                  estimate, resampling decision and uniform; commits or rolls
 //                  back the step; the fixed-point CDF prefixes of the chunks
+//                  (k_merge_one: both, up to 262,144 particles)
 //   k_anc          systematic resampling: one wave per segment of 1024
 //                  particles, each particle's run of output slots from the
 //                  segment's CDF
 //   k_fill         the slots of heavy segments queued by k_anc (concentrated
-//                  weights), in chunks of tiles
+//                  weights), in chunks of tiles (k_anc_all: both, up to 1024
+//                  segments, with helper waves instead of a queue)
 //   (or k_rna: RNA of Section 3, one wave or workgroup per group of particles;
 //                  k_arna_* for ARNA; k_rpa_* after the ancestors for RPA)
 #include "ppf_internal.hpp"
@@ -3432,9 +3434,11 @@ __global__ __launch_bounds__(256) void k_dlb_entries(int32_t kind, const int32_t
 // track, one workgroup per work item (track, index of the track's block,
 // chunk, segment or group) from a list built on the host, with the track's
 // model and buffers read from device arrays.
+
 // A pointer that was read from memory, as one to global memory (which it is):
 // the compiler otherwise has to use flat accesses, which also occupy the LDS path
-// and wait on its counter.
+// and wait on its counter (256 tracks, 11.7 M particles: the fused step 287 -> 264 us,
+// the wide one 59.9 -> 56.1).
 template <class T>
 __device__ __forceinline__ T* as_global(T* p) {
   return (T*)(__attribute__((address_space(1))) T*)reinterpret_cast<uintptr_t>(p);
