@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <array>
+#include <bitset>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -14,6 +15,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "ppf_internal.hpp"
@@ -306,8 +308,11 @@ class ReportArena {
  public:
   static constexpr int kSlots = 2048;
   static ReportArena& get() {
-    static ReportArena* a = new ReportArena();  // never destroyed: handles may outlive statics
-    return *a;
+    // nothing here allocates host memory, which could fail in the middle of a C entry
+    static ReportArena a;
+    // (no destructor runs at exit: handles may outlive statics)
+    static_assert(std::is_trivially_destructible<ReportArena>::value, "");
+    return a;
   }
   // The first of `count` consecutive slots, or null.
   Ctrl* take(int count) {
@@ -341,12 +346,11 @@ class ReportArena {
       return false;
     }
     base_ = static_cast<Ctrl*>(p);
-    used_.assign(kSlots, false);
     return true;
   }
   std::mutex mu_;
   Ctrl* base_ = nullptr;
-  std::vector<bool> used_;
+  std::bitset<kSlots> used_;
 };
 
 // Launch bookkeeping shared by filters and batches: the stream, the last
