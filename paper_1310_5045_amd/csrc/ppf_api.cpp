@@ -134,6 +134,8 @@ Model make_model(const ppf_params* p) {
   m.inv2sig2 = 1.0 / (2.0 * sg * sg);
   m.lognorm_obs = (double)m.P * (double)m.P * std::log(sg * std::sqrt(2.0 * M_PI));
   m.is2 = 2.0 * m.inv2s2;
+  m.cx_max = (int32_t)std::min<int64_t>((int64_t)m.W + m.P, INT32_MAX);
+  m.cy_max = (int32_t)std::min<int64_t>((int64_t)m.H + m.P, INT32_MAX);
   // ratio of consecutive 1-D Gaussian factors at unit pixel steps from -h
   const int h = (m.P - 1) / 2;
   for (int d = 0; d < ppf::kMaxPatch; ++d)

@@ -185,6 +185,7 @@ struct Model {
   double s_psf;          // s
   double sig;            // sigma_xi
   double is2;            // 1 / s^2
+  int32_t cx_max, cy_max;  // patch-centre clamp: W + P and H + P, at most INT_MAX
   // ARNA (group, G and moved = the largest exchange as for RNA)
   int32_t arna;          // adaptive RNA
   int32_t arna_mu_min;   // the smallest exchange, floor(arna_min n)

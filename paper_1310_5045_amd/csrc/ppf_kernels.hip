@@ -949,12 +949,13 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   const double ry = floor((double)o.y + 0.5);
   const double fx = (double)o.x - rx;
   const double fy = (double)o.y - ry;
-  // addresses only: far-away centres are clamped to [-P, W + P] x [-P, H + P],
+  // addresses only: far-away centres are clamped to [-P, W + P] x [-P, H + P]
+  // (cx_max, cy_max: on the host, as W + P may pass the largest int),
   // where the whole patch already lies outside the frame (its pixels read as
   // background); a NaN centre reads as 0 (its weight is NaN: the step is rolled
   // back)
-  const int cx = min(max(cvt_sat_i32(rx), -P), m.W + P);
-  const int cy = min(max(cvt_sat_i32(ry), -P), m.H + P);
+  const int cx = min(max(cvt_sat_i32(rx), -P), m.cx_max);
+  const int cy = min(max(cvt_sat_i32(ry), -P), m.cy_max);
   // The 1-D Gaussian factors of Eq. 3 at the patch's pixel offsets. Only
   // their products g_x g_y enter the likelihood, so g_x is taken relative to
   // its first value, which moves into the first g_y: three exps per particle
