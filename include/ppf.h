@@ -271,18 +271,25 @@ int ppf_step(ppf_handle h, const float* obs_dev);
 
 /*
  * Graph mode (1 on, 0 off; off after create). When on, the next ppf_step
- * records the step's kernel launches into a HIP graph instead of launching
- * them, and that step and every later one launch the graph (hipGraphLaunch)
- * with its frame argument pointed at the call's obs_dev; results are the
- * same as without the graph. A step of at most 12 launches is launched
- * directly all the same, which is the faster way to run it (RPA over more than
- * 8192 groups takes more). The launch sequence of a step does not depend
+ * records the step's kernel launches into a HIP graph. Where replaying it is
+ * the better way to run the step, that step and every later one launch the
+ * graph (hipGraphLaunch) with its frame argument pointed at the call's obs_dev;
+ * else they are launched directly, as without graph mode. Replayed are steps of
+ * more than 12 launches (RPA with sorted lists, PPF_DLB_SGS, over more than 8192
+ * groups) and the steps of large batches over many patch sizes (see
+ * ppf_batch_set_graph); ppf_graph_launches tells which. Results are the same
+ * either way. The launch sequence of a step does not depend
  * on the filter's state (every decision is taken on the device), so one
  * recording serves all steps. Switching syncs the handle's stream and drops
  * the recorded graph. ESTATE while kernel timing (ppf_profile_enable) is on:
  * the two exclude each other.
  */
 int ppf_set_graph(ppf_handle h, int enable);
+
+/* Kernel launches in the graph that the handle's steps replay; 0 when steps are
+ * launched directly (graph mode off, no step since it was switched on or its
+ * graph dropped, or a step that is faster so). EINVAL for a null launches. */
+int ppf_graph_launches(ppf_handle h, int32_t* launches);
 
 /*
  * Workgroup shapes of the spot-model step kernel for patches up to 13 x 13
@@ -542,9 +549,13 @@ int ppf_batch_reset(ppf_batch h);
 int ppf_step_batched(ppf_batch h, const float* obs_dev);
 
 /* Graph mode of a batch, as ppf_set_graph: one HIP graph holds every launch
- * of a batched step (one step launch for all patch sizes up to 13, one per
- * wider size, then the merge and resampling launches). */
+ * of a batched step (one step launch for all patch sizes up to 13, or two, one
+ * per wider size, then the merge and resampling launches), with the step
+ * launches side by side. Replayed are steps of more than 12 launches, and those
+ * of six or more step launches that take 4096 workgroups (2^20 particles) or
+ * more. */
 int ppf_batch_set_graph(ppf_batch h, int enable);
+int ppf_batch_graph_launches(ppf_batch h, int32_t* launches);
 
 /*
  * Workgroup shapes of a batch's fused step launches, by candidate:

@@ -113,6 +113,7 @@ _SIGS = {
     "ppf_reset": (ctypes.c_int, [ctypes.c_void_p]),
     "ppf_step": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p]),
     "ppf_set_graph": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int]),
+    "ppf_graph_launches": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32)]),
     "ppf_set_shape": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32]),
     "ppf_autotune": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
                                     ctypes.POINTER(ctypes.c_double),
@@ -162,6 +163,7 @@ _SIGS = {
     "ppf_batch_reset": (ctypes.c_int, [ctypes.c_void_p]),
     "ppf_step_batched": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p]),
     "ppf_batch_set_graph": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int]),
+    "ppf_batch_graph_launches": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32)]),
     "ppf_batch_set_shapes": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32]),
     "ppf_batch_autotune": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
                                           ctypes.POINTER(ctypes.c_double),
@@ -374,8 +376,15 @@ class Filter:
         return out
 
     def graph(self, on: bool = True):
-        """Graph mode: steps replay one recorded HIP graph of their launches."""
+        """Graph mode: steps of many launches replay one recorded HIP graph of
+        them, shorter ones are launched directly (see graph_launches)."""
         _check(lib().ppf_set_graph(self.handle, 1 if on else 0), self.handle)
+
+    def graph_launches(self) -> int:
+        """Launches in the graph that steps replay; 0 when they are launched directly."""
+        n = ctypes.c_int32()
+        _check(lib().ppf_graph_launches(self.handle, ctypes.byref(n)), self.handle)
+        return n.value
 
     def set_shape(self, shape: int):
         """Workgroup shape of the step kernel (see PPF_NUM_SHAPES)."""
@@ -503,8 +512,15 @@ class Batch:
         return x, lw, anc
 
     def graph(self, on: bool = True):
-        """Graph mode: batched steps replay one recorded HIP graph."""
+        """Graph mode: batched steps replay one recorded HIP graph where that is
+        the faster way (see graph_launches)."""
         self._chk(lib().ppf_batch_set_graph(self.handle, 1 if on else 0))
+
+    def graph_launches(self) -> int:
+        """Launches in the graph that steps replay; 0 when they are launched directly."""
+        n = ctypes.c_int32()
+        self._chk(lib().ppf_batch_graph_launches(self.handle, ctypes.byref(n)))
+        return n.value
 
     def set_shapes(self, candidate: int):
         """Workgroup shapes of the fused step launches (candidates 0-2)."""

@@ -452,18 +452,35 @@ struct Runner {
     events.clear();
     return PPF_OK;
   }
-  // Graph mode: a step of more than kGraphLaunches launches is recorded once
-  // into a HIP graph (the first step
-  // after enabling) and replayed, pointed at each call's frame. A step of
-  // fewer is launched directly: a replay costs the host some 20 us and the GPU
-  // 5 us a step whatever it holds. Per step, host and in all, launched and
-  // replayed: 3 launches at 4096 particles 11 / 21 and 23 / 25 us, 4 at 2^20 14 /
-  // 44 and 18 / 49 us, 4 of RNA 16 / 60 and 20 / 65 us, 6 of 256 tracks 17 / 386
-  // and 48 / 390 us; 22 of RPA over sorted lists 70 / 124 and 35 / 127 us, where
-  // the replay at least leaves the host free.
+  // Graph mode: a step is recorded into a HIP graph (the first step after
+  // enabling), and replayed from then on, pointed at each call's frame, where
+  // that pays; else the recording is dropped and steps are launched directly. A
+  // replay costs the host some 20 us and the GPU 3-5 us a step whatever it
+  // holds. Per step, host and in all, launched and replayed: 3 launches at 4096
+  // particles 14 / 19 and 19 / 22 us, 4 at 2^20 17 / 42 and 17 / 47 us, 4 of RNA
+  // 16 / 78 and 17 / 83 us, 5 of 256 tracks 17 / 332 and 40 / 339 us, 10 of RPA
+  // (greedy, 16,384 groups, 2^20 particles) 39 / 65 and 21 / 68 us. It pays
+  // - for more than kGraphLaunches launches (RPA over sorted lists, 18 to 24),
+  //   where it leaves the host free: 16,384 groups of 2^20 particles 72 / 118 and
+  //   30 / 119 us, of 2^16 particles 67 / 101 and 29 / 91 us;
+  // - for a batch with kGraphGroup step launches or more (one for all patch
+  //   sizes up to 13, or two, and one per wider size) of kGraphGroupBlocks
+  //   workgroups in all: the graph runs them side by side, so that one's last
+  //   workgroups do not leave the chip idle. A track of 200,000 particles per
+  //   size, launched and replayed: 5 launches 103 / 103 us, 6 launches 119 /
+  //   105, 7 launches 146 / 123, 8 launches 151 / 141. Of 50,000 (1200 to 2000
+  //   workgroups) 64 / 74, 70 / 75, 82 / 81 and 88 / 78, of 2000 61 / 66, 63 /
+  //   71, 76 / 76 and 82 / 87. With 4 launches the two are within 3 % from
+  //   300,000 particles on, with fewer a replay is slower.
   static constexpr size_t kGraphLaunches = 12;
+  static constexpr size_t kGraphGroup = 6;
+  static constexpr int64_t kGraphGroupBlocks = 4096;
+  static bool replay_pays(const ppf::StepGraph& g) {
+    return g.launches() > kGraphLaunches ||
+           (g.group_launches() >= kGraphGroup && g.group_blocks() >= kGraphGroupBlocks);
+  }
   bool graph_on = false;
-  bool graph_direct = false;  // this step's launches are too few
+  bool graph_direct = false;  // a replay of this step would not pay
   std::unique_ptr<ppf::StepGraph> graph;
   void drop_graph() {
     graph.reset();
@@ -474,6 +491,11 @@ struct Runner {
     if (hipStreamSynchronize(stream) != hipSuccess) return fail(PPF_EDEVICE, "sync");
     graph_on = on != 0;
     drop_graph();
+    return PPF_OK;
+  }
+  int graph_launches(int32_t* n) {
+    if (!n) return fail(PPF_EINVAL, "null count");
+    *n = graph ? (int32_t)graph->launches() : 0;
     return PPF_OK;
   }
   // Enqueues one step: enqueue() itself, or the graph of its launches.
@@ -487,7 +509,7 @@ struct Runner {
       const int rc = enqueue();
       g->stop();
       if (rc) return rc;
-      if (g->launches() <= kGraphLaunches) {
+      if (!replay_pays(*g)) {
         graph_direct = true;
         return enqueue();
       }
@@ -717,6 +739,11 @@ int ppf_step(ppf_handle h, const float* obs_dev) {
 int ppf_set_graph(ppf_handle h, int enable) {
   if (!h) return PPF_ESTATE;
   return h->graph_enable(enable);
+}
+
+int ppf_graph_launches(ppf_handle h, int32_t* launches) {
+  if (!h) return PPF_ESTATE;
+  return h->graph_launches(launches);
 }
 
 int ppf_set_shape(ppf_handle h, int32_t shape) {
@@ -1295,6 +1322,11 @@ int ppf_step_batched(ppf_batch h, const float* obs_dev) {
 int ppf_batch_set_graph(ppf_batch h, int enable) {
   if (!h) return PPF_ESTATE;
   return h->graph_enable(enable);
+}
+
+int ppf_batch_graph_launches(ppf_batch h, int32_t* launches) {
+  if (!h) return PPF_ESTATE;
+  return h->graph_launches(launches);
 }
 
 int ppf_batch_set_shapes(ppf_batch h, int32_t candidate) {

@@ -328,6 +328,9 @@ class StepGraph {
   hipError_t begin(const float* frame);
   void stop();
   size_t launches() const { return nodes_.size(); }  // recorded
+  // The largest group recorded (see group_begin): its launches and workgroups.
+  size_t group_launches() const { return group_launches_; }
+  int64_t group_blocks() const { return group_blocks_; }
   hipError_t instantiate();
   bool ready() const { return exec_ != nullptr; }
   hipError_t set_frame(const float* frame);
@@ -360,6 +363,9 @@ class StepGraph {
   std::vector<hipGraphNode_t> deps_;   // what the next node depends on
   bool in_group_ = false;
   std::vector<hipGraphNode_t> group_;  // the nodes of the open group
+  int64_t open_blocks_ = 0;            // and their workgroups
+  size_t group_launches_ = 0;
+  int64_t group_blocks_ = 0;
 };
 
 // Launches between these two calls may run concurrently when a graph records

@@ -3757,10 +3757,12 @@ hipError_t StepGraph::add(const void* fn, dim3 grid, dim3 block, std::unique_ptr
   const hipGraphNode_t* deps = deps_.empty() ? nullptr : deps_.data();
   const hipError_t e = hipGraphAddKernelNode(&n.node, graph_, deps, deps_.size(), &n.params);
   if (e != hipSuccess) return e;
-  if (in_group_)
+  if (in_group_) {
     group_.push_back(n.node);
-  else
+    open_blocks_ += (int64_t)grid.x * grid.y * grid.z;
+  } else {
     deps_.assign(1, n.node);
+  }
   nodes_.push_back(std::move(n));
   return hipSuccess;
 }
@@ -3768,11 +3770,16 @@ hipError_t StepGraph::add(const void* fn, dim3 grid, dim3 block, std::unique_ptr
 void StepGraph::group_begin() {
   in_group_ = true;
   group_.clear();
+  open_blocks_ = 0;
 }
 
 void StepGraph::group_end() {
   in_group_ = false;
   if (!group_.empty()) deps_ = group_;
+  if (group_.size() > group_launches_) {
+    group_launches_ = group_.size();
+    group_blocks_ = open_blocks_;
+  }
   group_.clear();
 }
 
