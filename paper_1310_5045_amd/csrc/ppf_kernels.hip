@@ -1816,6 +1816,11 @@ __device__ __forceinline__ void merge_one(const Model& m, const Buffers& b, int 
   __shared__ MergeSh sh[kOneMergeChunks];
   __shared__ double cr[kOneMergeChunks * kRec], crg[kOneMergeChunks * kNGrad];
   const int sub = wave_index() >> 2, t = threadIdx.x & 255, w = wave_index() & 3;
+  // In a batch the workgroup has waves for the track with the most chunks: the others'
+  // idle ones end here (whole waves, which the barriers below then do not wait for)
+  // instead of merging nothing beside those of the other tracks. 2000 tracks of one
+  // chunk and one of four: 37 -> 20 us, and 26 in two launches.
+  if (sub >= b.nch) return;
   if constexpr (GRAD) {
     __shared__ double fac[256 * kOneMergeChunks], part[64 * kOneMergeChunks];
     merge_chunk_deriv(m, b, sub, t, w, sh[sub], fac + 256 * sub, part + 64 * sub,
