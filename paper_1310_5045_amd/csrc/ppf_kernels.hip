@@ -2306,6 +2306,11 @@ __device__ __forceinline__ void anc_help(const Model& m, const Buffers& b, const
 // others work. With no heavy segment (most steps) that takes no longer than the
 // segments themselves; k_fill's launch for an empty queue costs 2-4 us and a gap.
 // Beyond, a helper's look over all segments would outlast a launch.
+// The chunks of the lightest heavy segment, which spans at least kCoopTiles kSlotTile - 2
+// slots, times as many segments: the most chunks there can be.
+static_assert(kHelpWaves >= (kCoopTiles + kChunkTiles) / kChunkTiles *
+                                (kWave * kHelpPerLane * kSegItems / (kCoopTiles * kSlotTile - 2)),
+              "a helper wave per chunk");
 template <bool LOG>
 __global__ __launch_bounds__(kWave) void k_anc_all(Model m, Buffers b, WeightSrc ws) {
   const int nseg = (int)b.nseg, j = (int)blockIdx.x;
