@@ -1055,12 +1055,15 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   // each. Measured: the first frame of 250,007 particles with 25 x 25 patches
   // from a Gaussian prior 278 -> 67 us; a step of 2^20 particles that lost the
   // spot (9 x 9) 44.5 -> 34.7 us. Gradient mode keeps the two choices: a third
-  // cost its kernel 2 % (registers) on clouds that never need it.
+  // cost its kernel 2 % (registers) on clouds that never need it. Patches of 1 x 1
+  // and 3 x 3 keep them too: staging a box takes more loads than their particles'
+  // one or nine each (2^22 particles spread over 68 x 68 pixels, staged and from
+  // the frame: 1 x 1 138 and 85 us, 3 x 3 149 and 122; 5 x 5 160 and 197).
   constexpr int kAll = TILE + kSq;
   enum { kFrame, kFloat, kDouble };
   int single = kFrame;  // uniform in a wave
   int sx0 = tx0, sy0 = ty0, sw = 0, sbase = 0;
-  if (!GRAD && !use_lds) {
+  if (!GRAD && P >= 5 && !use_lds) {
     int64_t bw = tw64, bh = th64, cap = kAll;
     int e0 = t, step = 256;
     if (bw * bh > 2 * (int64_t)kAll) {  // uniform in the workgroup
