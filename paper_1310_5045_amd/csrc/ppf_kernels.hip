@@ -769,11 +769,45 @@ __device__ __forceinline__ void patch_single(const T* __restrict__ p0, int tw, d
 
 // The same sums read straight from the frame (waves whose patches fit no LDS
 // tile); pixels outside the frame read as the background.
+//
+// Below 13 x 13 a wave whose patches all lie inside loads a row's pixels
+// together, from one 32-bit offset; with a check and a branch per pixel each load
+// waits for the one before it. Then more waves on a CU (as the LDS of these sizes
+// allows since their table takes half the tile) only make the frame's lines push each
+// other out of the cache: 2^22 particles spread over 90 x 90 pixels, 5 x 5 patches
+// 201 us a step with five workgroups on a CU and 221 with six, 9 x 9 472 and 521; with
+// the rows' loads together 134 and 213. (From 13 x 13 on registers hold the number of
+// workgroups where it was, and the second loop spills them in the six-wave shape.)
 template <int P>
 __device__ __forceinline__ void patch_global(const float* __restrict__ obs, int u0, int v0,
                                              int W, int H, double bsub, const double (&gx)[P],
                                              double gy, double by, const double* gstep,
                                              double& X, double& G2y, double& sd2) {
+  if constexpr (P < kFusedMaxP) {
+    const bool inside = u0 >= 0 && v0 >= 0 && u0 <= W - P && v0 <= H - P;
+    if ((int64_t)W * H <= (int64_t)1 << 30 && __ballot(!inside) == 0) {  // byte offsets of 32 bits
+      uint32_t at = 4u * ((uint32_t)v0 * (uint32_t)W + (uint32_t)u0);
+#pragma unroll 1
+      for (int dy = 0; dy < P; ++dy) {
+        float z[P];
+#pragma unroll
+        for (int dx = 0; dx < P; ++dx)
+          z[dx] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(obs + dx) + at);
+        double rd = 0.0;
+#pragma unroll
+        for (int dx = 0; dx < P; ++dx) {
+          const double d = (double)z[dx] - bsub;
+          rd = dx == 0 ? d : fma(d, gx[dx], rd);
+          sd2 = fma(d, d, sd2);
+        }
+        X = fma(gy, rd, X);
+        G2y = fma(gy, gy, G2y);
+        gy *= gstep[dy] * by;
+        at += 4u * (uint32_t)W;
+      }
+      return;
+    }
+  }
 #pragma unroll 1
   for (int dy = 0; dy < P; ++dy) {
     const int v = v0 + dy;
@@ -1055,15 +1089,17 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   // each. Measured: the first frame of 250,007 particles with 25 x 25 patches
   // from a Gaussian prior 278 -> 67 us; a step of 2^20 particles that lost the
   // spot (9 x 9) 44.5 -> 34.7 us. Gradient mode keeps the two choices: a third
-  // cost its kernel 2 % (registers) on clouds that never need it. Patches of 1 x 1
-  // and 3 x 3 keep them too: staging a box takes more loads than their particles'
-  // one or nine each (2^22 particles spread over 68 x 68 pixels, staged and from
-  // the frame: 1 x 1 138 and 85 us, 3 x 3 149 and 122; 5 x 5 160 and 197).
+  // cost its kernel 2 % (registers) on clouds that never need it. Patches up to
+  // 7 x 7 keep them too: staging a box takes more loads than reading their pixels,
+  // as long as the wave's patches lie in the frame (2^22 particles spread over 68 x
+  // 68 pixels, staged and from the frame: 1 x 1 138 and 85 us, 3 x 3 149 and 98, 5 x
+  // 5 157 and 121, 7 x 7 170 and 141, 9 x 9 187 and 189; over 44 x 44 pixels 5 x 5
+  // 125 and 107, 7 x 7 139 and 121, 9 x 9 162 and 166).
   constexpr int kAll = TILE + kSq;
   enum { kFrame, kFloat, kDouble };
   int single = kFrame;  // uniform in a wave
   int sx0 = tx0, sy0 = ty0, sw = 0, sbase = 0;
-  if (!GRAD && P >= 5 && !use_lds) {
+  if (!GRAD && P >= 9 && !use_lds) {
     int64_t bw = tw64, bh = th64, cap = kAll;
     int e0 = t, step = 256;
     if (bw * bh > 2 * (int64_t)kAll) {  // uniform in the workgroup
