@@ -1089,17 +1089,18 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   // each. Measured: the first frame of 250,007 particles with 25 x 25 patches
   // from a Gaussian prior 278 -> 67 us; a step of 2^20 particles that lost the
   // spot (9 x 9) 44.5 -> 34.7 us. Gradient mode keeps the two choices: a third
-  // cost its kernel 2 % (registers) on clouds that never need it. Patches up to
-  // 7 x 7 keep them too: staging a box takes more loads than reading their pixels,
-  // as long as the wave's patches lie in the frame (2^22 particles spread over 68 x
-  // 68 pixels, staged and from the frame: 1 x 1 138 and 85 us, 3 x 3 149 and 98, 5 x
-  // 5 157 and 121, 7 x 7 170 and 141, 9 x 9 187 and 189; over 44 x 44 pixels 5 x 5
-  // 125 and 107, 7 x 7 139 and 121, 9 x 9 162 and 166).
+  // cost its kernel 2 % (registers) on clouds that never need it. So do patches up to
+  // 3 x 3, and 5 x 5 and 7 x 7 where the box lies in the frame (patch_global then
+  // has its quick form): staging takes more loads than reading their pixels (2^22
+  // particles spread over 68 x 68 pixels, staged and from the frame: 1 x 1 138 and 85
+  // us, 3 x 3 149 and 98, 5 x 5 157 and 121, 7 x 7 170 and 141, 9 x 9 187 and 189; over
+  // 44 x 44 pixels 5 x 5 125 and 107, 7 x 7 139 and 121, 9 x 9 162 and 166).
   constexpr int kAll = TILE + kSq;
   enum { kFrame, kFloat, kDouble };
   int single = kFrame;  // uniform in a wave
   int sx0 = tx0, sy0 = ty0, sw = 0, sbase = 0;
-  if (!GRAD && P >= 9 && !use_lds) {
+  const bool inside = tx0 >= 0 && ty0 >= 0 && mxx < m.W - h && mxy < m.H - h;
+  if (!GRAD && !use_lds && (P >= 9 || (P >= 5 && !inside))) {
     int64_t bw = tw64, bh = th64, cap = kAll;
     int e0 = t, step = 256;
     if (bw * bh > 2 * (int64_t)kAll) {  // uniform in the workgroup
@@ -1855,11 +1856,6 @@ __device__ __forceinline__ void merge_one(const Model& m, const Buffers& b, int 
   __shared__ MergeSh sh[kOneMergeChunks];
   __shared__ double cr[kOneMergeChunks * kRec], crg[kOneMergeChunks * kNGrad];
   const int sub = wave_index() >> 2, t = threadIdx.x & 255, w = wave_index() & 3;
-  // In a batch the workgroup has waves for the track with the most chunks: the others'
-  // idle ones end here (whole waves, which the barriers below then do not wait for)
-  // instead of merging nothing beside those of the other tracks. 2000 tracks of one
-  // chunk and one of four: 37 -> 20 us, and 26 in two launches.
-  if (sub >= b.nch) return;
   if constexpr (GRAD) {
     __shared__ double fac[256 * kOneMergeChunks], part[64 * kOneMergeChunks];
     merge_chunk_deriv(m, b, sub, t, w, sh[sub], fac + 256 * sub, part + 64 * sub,
@@ -3576,7 +3572,13 @@ __global__ __launch_bounds__(256) void k_merge_batch(const Model* __restrict__ m
 // gap between them in two launches.)
 __global__ __launch_bounds__(256 * kOneMergeChunks) void k_merge_one_batch(
     const Model* __restrict__ ms, const Buffers* __restrict__ bs) {
-  merge_one<false>(ms[blockIdx.x], track_buffers(bs[blockIdx.x]), 0, 0.0);
+  const Buffers b = track_buffers(bs[blockIdx.x]);
+  // The workgroup has waves for the track with the most chunks: this one's idle waves
+  // end here (whole waves, which the barriers of the merge then do not wait for) instead
+  // of merging nothing beside those of other tracks. 2000 tracks of one chunk and one
+  // of four: 37 -> 20 us, and 26 in two launches.
+  if ((wave_index() >> 2) >= b.nch) return;
+  merge_one<false>(ms[blockIdx.x], b, 0, 0.0);
 }
 __global__ __launch_bounds__(256) void k_merge_final_batch(const Model* __restrict__ ms,
                                                            const Buffers* __restrict__ bs) {
