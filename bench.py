@@ -248,7 +248,7 @@ def run_multitrack(args, w):
         del src, dst
     b = ppf.Batch(ps)
     graph = args.launch == "graph"
-    gpu_ms, wall, kt, tuned, _ = timed_steps(torch, b, frames, K, Wm, T, graph, args.shape)
+    gpu_ms, wall, kt, tuned, _, replayed = timed_steps(torch, b, frames, K, Wm, T, graph, args.shape)
     sts = b.stats()
     ntot = sum(int(p.n_particles) for p in ps)
     flops = sum(4 * ppf.patch_size(p) ** 2 * int(p.n_particles) for p in ps)
@@ -281,7 +281,7 @@ def run_multitrack(args, w):
                    "n_max": max(int(p.n_particles) for p in ps),
                    "patches": sorted({ppf.patch_size(p) for p in ps}),
                    "frame": [w["W"], w["H"]], "resampling": "systematic", "frames_timed": K,
-                   "launch": args.launch, "autotune": tuned},
+                   "launch": args.launch, "graph_launches": replayed, "autotune": tuned},
         "roofline": {"bound": "alu", "kernel": "k_step (all patch sizes)",
                      "achieved": achieved_tf, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved_tf / FP64_VECTOR_PEAK_TFLOPS,
@@ -301,7 +301,7 @@ def run_multitrack(args, w):
                              background=10.0, noise_sd=3.0, seed=1)
     pframes = torch.from_numpy(pmv.frames).cuda()
     pf = ppf.Filter(make_params(ppf, pw, ppf.INIT_UNIFORM_ZORDER))
-    pms, _, _, _, _ = timed_steps(torch, pf, pframes, K, Wm, pw["T"], False, None)
+    pms, _, _, _, _, _ = timed_steps(torch, pf, pframes, K, Wm, pw["T"], False, None)
     check_state(ppf, pf, pw, pmv, (K - 1) % pw["T"], 0)
     pf.close()
     plain = pw["n"] * K / (pms / 1e3)
@@ -521,11 +521,13 @@ def timed_steps(torch, f, frames, K, Wm, T, graph, shape):
     """K steps of filter or batch f from a fresh initial cloud, after Wm
     warm-up steps: (GPU ms of the K steps between two events on f's stream,
     wall s, per-kernel times, autotuner result or None, shape the steps ran
-    with). With shape=None the autotuner picks the step kernel's workgroup
-    shape on the warm filter two steps before the end of the warm-up (so that
-    a graph is recorded again before the timed steps); otherwise the given
-    shape is set before the warm-up. With graph=True the timed steps replay
-    the step's HIP graph, and the per-kernel times come from a second pass
+    with, launches in the graph that the steps replayed). With shape=None the
+    autotuner picks the step kernel's workgroup shape on the warm filter two
+    steps before the end of the warm-up (so that a graph is recorded again
+    before the timed steps); otherwise the given shape is set before the
+    warm-up. With graph=True the timed steps run in graph mode, in which the
+    library replays a HIP graph of long steps and launches short ones directly
+    (0 launches replayed), and the per-kernel times come from a second pass
     over the same K steps with plain launches and kernel timing on (the two
     exclude each other)."""
     f.graph(graph)
@@ -557,6 +559,7 @@ def timed_steps(torch, f, frames, K, Wm, T, graph, shape):
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     gpu_ms = ev0.elapsed_time(ev1)
+    replayed = f.graph_launches()
     if graph:
         # the same K steps again from the same initial cloud: they end in the
         # same state, bit for bit, which the caller then reads
@@ -566,7 +569,7 @@ def timed_steps(torch, f, frames, K, Wm, T, graph, shape):
         for k in range(K):
             f.step(frames[k % T])
     kt = f.kernel_times()
-    return gpu_ms, wall, kt, tuned, ran
+    return gpu_ms, wall, kt, tuned, ran, replayed
 
 
 def host_cpu():
@@ -759,7 +762,8 @@ def main():
                     help="skip the second measurement from the other initial cloud")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--launch", default="stream", choices=["stream", "graph"],
-                    help="timed steps as plain launches or as replays of one HIP graph")
+                    help="timed steps as plain launches or in graph mode (long steps replay a HIP "
+                         "graph, short ones are launched directly)")
     ap.add_argument("--shape", type=int, default=None,
                     help="step-kernel workgroup shape (batched: shape candidate) for every "
                          "step; default: the autotuner picks it during the warm-up")
@@ -851,13 +855,13 @@ def run(args):
         # the same configuration without derivatives, launched the same way,
         # for the ratio
         pf = ppf.Filter(make_params(ppf, w, init_kind))
-        pms, _, pkt, _, _ = timed_steps(torch, pf, frames, K, Wm, T, graph, args.shape)
+        pms, _, pkt, _, _, _ = timed_steps(torch, pf, frames, K, Wm, T, graph, args.shape)
         pf.close()
         plain = {"value": w["n"] * K / (pms / 1e3), "ms_per_step": pms / K,
                  "k_step_ms": pkt.get("k_step", (1, 0.0))[1] / K}
     f = ppf.Filter(make_params(ppf, w, init_kind, grad=w.get("grad", 0)))
     scheme = w.get("scheme", (0,))[0]
-    gpu_ms, wall, kt, tuned, ran = timed_steps(torch, f, frames, K, Wm, T, graph, args.shape)
+    gpu_ms, wall, kt, tuned, ran, replayed = timed_steps(torch, f, frames, K, Wm, T, graph, args.shape)
     err, st = check_state(ppf, f, w, mv, (K - 1) % T, scheme)
     n = w["n"]
     ms_per_step = gpu_ms / K
@@ -902,6 +906,7 @@ def run(args):
                                   + ("" if w["thr"] == float("inf")
                                      else f" when ESS < {w['thr']:.0f}")),
                    "init": args.init, "frames_timed": K, "launch": args.launch,
+                   "graph_launches": replayed,
                    "autotune": tuned, "shape": ran},
         "roofline": {"bound": "alu", "kernel": "k_step", "achieved": achieved_tf,
                      "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
@@ -942,7 +947,7 @@ def run(args):
         alt = "stratified" if args.init == "uniform" else "uniform"
         ak = INIT_KINDS[alt](ppf)
         fa = ppf.Filter(make_params(ppf, w, ak))
-        a_ms, _, akt, _, _ = timed_steps(torch, fa, frames, K, 2, T, graph, ran)
+        a_ms, _, akt, _, _, _ = timed_steps(torch, fa, frames, K, 2, T, graph, ran)
         a_err, a_st = check_state(ppf, fa, w, mv, (K - 1) % T, scheme)
         fa.close()
         out["init_alternative"] = {"init": alt, "value": n * K / (a_ms / 1e3),

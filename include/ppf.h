@@ -163,7 +163,10 @@ typedef struct ppf_ctx* ppf_handle;
  *               theta (see ppf_grad). Needs the spot model, systematic
  *               resampling and ess_threshold = +INFINITY; the workspace then
  *               also holds 2 x 7 tangents per particle (fp32) and 9 doubles
- *               per 256-particle block. 0: none.
+ *               per 256-particle block. States, weights, ancestors and the
+ *               log-likelihood are those of grad = 0 bit for bit; the MMSE
+ *               estimate and the ESS too above 262,144 particles, and up to
+ *               there but for their last bits (summed in another order). 0: none.
  */
 typedef struct ppf_params {
   int32_t state_dim;
@@ -210,9 +213,9 @@ typedef struct ppf_stats_t {
 
 /* Per-kernel timing accumulated while profiling is enabled. Entries are
  * named for the step's timed units: "k_step", "k_merge" (both merge
- * launches), "k_resample" (the systematic resampling pass: the segment
- * launch and the launch that fills queued tile chunks, under one pair of
- * events), "k_rna" (RNA and ARNA), "k_rpa", and "k_init", "k_gather",
+ * launches, or the one), "k_resample" (the systematic resampling pass: the
+ * segment launch and the launch that fills queued tile chunks, or one launch for
+ * both, under one pair of events), "k_rna" (RNA and ARNA), "k_rpa", and "k_init", "k_gather",
  * "k_logw" outside the step. */
 typedef struct ppf_kernel_time {
   char name[32];

@@ -71,12 +71,16 @@ constexpr int kFillGridBatch = 2048;  // waves of a batched fill, over all track
 // Batched steps run every patch size up to this one in a single launch (the
 // sizes that fit five waves per SIMD); wider patches launch per size.
 constexpr int kFusedMaxP = 13;
-constexpr int kSortTile = 1024;      // pairs per tile of the list scans and of small sorts
-constexpr int64_t kSortFold = 1 << 19;   // pairs up to which the scatter adds up the tiles' counts
+constexpr int kSortTile = 1024;  // pairs per tile of the list scans; the sort's smallest tile
+// Radix sort: up to kSortFold pairs tiles of 4096 whose counts the scatter adds up, below
+// kSortLarge tiles of 1024, from there on tiles of 4096 (measured beside the kernels).
+constexpr int64_t kSortFold = 1 << 19;
+constexpr int64_t kSortLarge = 1 << 22;
 constexpr unsigned kScanFold = 4096;  // list tiles up to which each adds up those before it
-constexpr int64_t kSortLarge = 1 << 22;  // pairs from which the radix sort takes 4096-pair tiles
 // RPA: up to kRankGroups groups are ranked by counting; up to kRpaScanN
-// particles the groups' offspring ranges are found by a look at every slot.
+// particles the groups' offspring ranges are found by a look at every slot (the plan and
+// routing of groups of 256, by a look and by search: 2^20 particles 26 and 33 us, 2^22 38
+// and 42, 2^23 62 and 61, 2^24 104 and 95).
 constexpr int kRankGroups = 8192;
 constexpr int64_t kRpaScanN = 1 << 22;
 // The allocation-free standalone resampler keeps its scratch in a device

@@ -2340,7 +2340,8 @@ __device__ __forceinline__ void anc_help(const Model& m, const Buffers& b, const
 // per segment, then helper waves for the heavy ones, which find them while the
 // others work. With no heavy segment (most steps) that takes no longer than the
 // segments themselves; k_fill's launch for an empty queue costs 2-4 us and a gap.
-// Beyond, a helper's look over all segments would outlast a launch.
+// Beyond, the helpers' look over all segments outlasts a launch: with 64 segments to
+// a lane 1.2 M particles take 18.9 us, and 11.7 in two launches; 2^21 31.6 and 12.7.
 // The chunks of the lightest heavy segment, which spans at least kCoopTiles kSlotTile - 2
 // slots, times as many segments: the most chunks there can be.
 static_assert(kHelpWaves >= (kCoopTiles + kChunkTiles) / kChunkTiles *
@@ -2751,8 +2752,9 @@ __global__ __launch_bounds__(256) void k_rpa_first(Model m, Buffers b) {
 // The whole plan for up to kRankGroups groups: group g's base in the stream is
 // the sum of the values before it in its side's order, taken over all groups by
 // 16 lanes (the values in LDS). G^2 compares: 10.6 us for 4096 groups, where the
-// radix sort and the scans of the lists were 16 launches and 80 us; the compares
-// would overtake them between 8192 and 16,384 groups.
+// radix sort and the scans of the lists were 16 launches and 80 us. A step of 2^20
+// particles: sorted greedy 66 us with 4096 groups, 77 with 8192, and 121 with 8256 by
+// sorting; greedy, whose lists need no sort, 64, 76, and 67 with 16,384 by the scans.
 template <bool SORTED>
 __global__ __launch_bounds__(256) void k_rpa_rank(Model m, Buffers b) {
   const Ctrl* c = b.ctrl;
@@ -2839,10 +2841,18 @@ __device__ __forceinline__ uint64_t rpa_value(const Buffers& b, int64_t n, int64
 // pairs long on average. Over 38 M pairs (608 MB a pass) it takes 156 us in
 // tiles of 4096, 192 us in tiles of 2048 and 243-261 us in tiles of 8192 (LDS
 // for one workgroup per CU); written straight from tiles of 1024, 16 bytes to a
-// run, it took 911 us. Below kSortLarge pairs the tiles are 1024 pairs, so that
-// enough workgroups run: 2^20 pairs take 11.0 us against 13.4 us in tiles of
-// 4096 (22 us before), the 304,000 entries of 152,000 groups' lists 135 us for
-// a schedule against 154 us.
+// run, it took 911 us. Three forms, by the number of pairs (radix_sort):
+// - up to kSortFold, tiles of 4096 by 1024 threads whose counts the scatter adds up
+//   itself: two launches a pass. A schedule waits for its launches: 32 list entries
+//   76 us, and 102 in the next form; 304,000 114 and 118; 2^19 119 and 125. (Where the
+//   stream is full anyway the next form's kernels are the shorter ones, in RPA's step
+//   76 us against 73 with 32,768 entries and 86 against 77 with 262,144.) The rows to
+//   add up grow with the square of the tiles: 1.6 M entries 257 us, and 207.
+// - up to kSortLarge, tiles of 1024 by 256 threads, so that enough workgroups run, and
+//   a launch of its own for the rows: 2^20 entries 139 us, and 154 in the next form.
+// - from there on tiles of 4096 by 256 threads and the same three launches: the
+//   Z-ordered initialisation of 2^22 particles 156 us, and 184 in tiles of 1024, of 2^23
+//   254 and 320 (of 2^21 the two are equal, 119 and 121).
 
 // The tile of a workgroup: consecutive tiles, whose runs of a digit are
 // neighbours in the output, go to workgroups of one XCD (workgroups are dealt
@@ -2880,9 +2890,7 @@ __device__ __forceinline__ void count_digit(uint32_t* h, uint32_t d, bool in) {
 }
 
 // FOLD: few tiles; their counts stay a row per tile and every workgroup of the
-// scatter adds up the rows itself, for which a launch of its own takes longer
-// (304,000 pairs in 75 tiles of 4096: a pass 14.7 us in two launches, against 15.4
-// us and a gap in three over tiles of 1024).
+// scatter adds up the rows itself, instead of a launch of its own for it.
 template <int T, int R, bool FOLD>
 __global__ __launch_bounds__(T) void k_radix_hist(const uint32_t* __restrict__ key, int64_t count,
                                                   int shift, uint32_t* __restrict__ hist,
