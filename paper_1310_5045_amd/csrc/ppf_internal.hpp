@@ -77,11 +77,13 @@ constexpr int kSortTile = 1024;  // pairs per tile of the list scans; the sort's
 constexpr int64_t kSortFold = 1 << 19;
 constexpr int64_t kSortLarge = 1 << 22;
 constexpr unsigned kScanFold = 4096;  // list tiles up to which each adds up those before it
-// RPA: up to kRankGroups groups are ranked by counting; up to kRpaScanN
+// RPA: up to kRankGroups groups are ranked by counting, under the greedy schedule, whose
+// lists need no sort, up to kRankGreedy (measured beside k_rpa_rank). Up to kRpaScanN
 // particles the groups' offspring ranges are found by a look at every slot (the plan and
 // routing of groups of 256, by a look and by search: 2^20 particles 26 and 33 us, 2^22 38
 // and 42, 2^23 62 and 61, 2^24 104 and 95).
 constexpr int kRankGroups = 8192;
+constexpr int kRankGreedy = 4096;
 constexpr int64_t kRpaScanN = 1 << 22;
 // The allocation-free standalone resampler keeps its scratch in a device
 // array of this many bytes, one per device for the life of the process.

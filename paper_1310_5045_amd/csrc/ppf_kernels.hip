@@ -775,8 +775,8 @@ __device__ __forceinline__ void patch_single(const T* __restrict__ p0, int tw, d
 // waits for the one before it. Then more waves on a CU (as the LDS of these sizes
 // allows since their table takes half the tile) only make the frame's lines push each
 // other out of the cache: 2^22 particles spread over 90 x 90 pixels, 5 x 5 patches
-// 201 us a step with five workgroups on a CU and 221 with six, 9 x 9 472 and 521; with
-// the rows' loads together 134 and 213. (From 13 x 13 on registers hold the number of
+// 201 us with five workgroups on a CU and 221 with six, 9 x 9 472 and 521; with the
+// rows' loads together 124 and 204. (From 13 x 13 on registers hold the number of
 // workgroups where it was, and the second loop spills them in the six-wave shape.)
 template <int P>
 __device__ __forceinline__ void patch_global(const float* __restrict__ obs, int u0, int v0,
@@ -1092,8 +1092,8 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   // cost its kernel 2 % (registers) on clouds that never need it. So do patches up to
   // 3 x 3, and 5 x 5 and 7 x 7 where the box lies in the frame (patch_global then
   // has its quick form): staging takes more loads than reading their pixels (2^22
-  // particles spread over 68 x 68 pixels, staged and from the frame: 1 x 1 138 and 85
-  // us, 3 x 3 149 and 98, 5 x 5 157 and 121, 7 x 7 170 and 141, 9 x 9 187 and 189; over
+  // particles spread over 68 x 68 pixels, staged and from the frame: a step 1 x 1 138 and
+  // 85 us, 3 x 3 149 and 98, 5 x 5 157 and 121, 7 x 7 170 and 141, 9 x 9 187 and 189; over
   // 44 x 44 pixels 5 x 5 125 and 107, 7 x 7 139 and 121, 9 x 9 162 and 166).
   constexpr int kAll = TILE + kSq;
   enum { kFrame, kFloat, kDouble };
@@ -2752,9 +2752,11 @@ __global__ __launch_bounds__(256) void k_rpa_first(Model m, Buffers b) {
 // The whole plan for up to kRankGroups groups: group g's base in the stream is
 // the sum of the values before it in its side's order, taken over all groups by
 // 16 lanes (the values in LDS). G^2 compares: 10.6 us for 4096 groups, where the
-// radix sort and the scans of the lists were 16 launches and 80 us. A step of 2^20
-// particles: sorted greedy 66 us with 4096 groups, 77 with 8192, and 121 with 8256 by
-// sorting; greedy, whose lists need no sort, 64, 76, and 67 with 16,384 by the scans.
+// radix sort and the scans of the lists were 16 launches and 80 us. Sorted greedy, a
+// step of 2^20 particles: 66 us with 4096 groups, 77 with 8192, and 121 with 8256 by
+// sorting. The greedy lists need no sort, only the scans' three launches (a step with
+// groups of 256, by counting and by scans: 2048 groups 50 and 56 us, 4096 64 and 66, 4608
+// 71 and 67, 8192 98 and 85; with groups of 4 40 and 46, 43 and 46, 45 and 46, 53 and 47).
 template <bool SORTED>
 __global__ __launch_bounds__(256) void k_rpa_rank(Model m, Buffers b) {
   const Ctrl* c = b.ctrl;
@@ -4037,7 +4039,7 @@ hipError_t launch_rpa(const Model& m, const Buffers& b, hipStream_t s) {
   hipError_t e = m.n <= kRpaScanN
                      ? launch_k(k_rpa_bounds, dim3(grid_for(m.n / 4 + 1, 256)), dim3(256), s, m, b)
                      : launch_k(k_rpa_first, dim3(grid_for(G + 1, 256)), dim3(256), s, m, b);
-  if (G <= kRankGroups) {
+  if (G <= (m.dlb == 1 ? kRankGroups : kRankGreedy)) {
     if (e == hipSuccess)
       e = launch_k(m.dlb == 1 ? k_rpa_rank<true> : k_rpa_rank<false>, dim3(grid_for(G, 16)),
                    dim3(256), s, m, b);
