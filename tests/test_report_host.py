@@ -62,7 +62,7 @@ def stand_in(tmp_path_factory):
 
 @pytest.mark.parametrize("fail_at", [0, 1, 2, 3])
 def test_query_out_of_memory(stand_in, fail_at):
-    preload = " ".join([stand_in] + os.environ.get("LD_PRELOAD", "").split())
+    preload = " ".join(os.environ.get("LD_PRELOAD", "").split() + [stand_in])
     r = subprocess.run([sys.executable, "-c", QUERY, stand_in, str(fail_at)], cwd=ROOT,
                        env=dict(os.environ, LD_PRELOAD=preload), capture_output=True, text=True,
                        timeout=120)
