@@ -770,35 +770,82 @@ __device__ __forceinline__ void patch_single(const T* __restrict__ p0, int tw, d
 // The same sums read straight from the frame (waves whose patches fit no LDS
 // tile); pixels outside the frame read as the background.
 //
-// Below 13 x 13 a wave whose patches all lie inside loads a row's pixels
-// together, from one 32-bit offset; with a check and a branch per pixel each load
-// waits for the one before it. Then more waves on a CU (as the LDS of these sizes
-// allows since their table takes half the tile) only make the frame's lines push each
-// other out of the cache: 2^22 particles spread over 90 x 90 pixels, 5 x 5 patches
-// 201 us with five workgroups on a CU and 221 with six, 9 x 9 472 and 521; with the
-// rows' loads together 124 and 204. (From 13 x 13 on registers hold the number of
-// workgroups where it was, and the second loop spills them in the six-wave shape.)
+// A check and a branch per pixel make each load wait for the one before it, and
+// then more waves on a CU (as the LDS up to 13 x 13 allows since their table takes
+// half the tile) only make the frame's lines push each other out of the cache: 2^22
+// particles spread over 90 x 90 pixels, 5 x 5 patches 201 us with five workgroups on
+// a CU and 221 with six, 9 x 9 472 and 521. So a row's pixels (C of them at a time,
+// as many as take no register more than the rest of the step) are loaded together,
+// from one 32-bit offset: 124 and 204 us. A wave with a patch over a border, below
+// 13 x 13, loads the frame's nearest column for the pixels beyond it and takes 0 for
+// them, and skips the columns and the rows that lie outside for all its patches:
+// 2^21 particles around the centre of a 512 x 512 frame, 200 pixels to a standard
+// deviation, 5 x 5 155 -> 75 us, 9 x 9 434 -> 183, 11 x 11 636 -> 246. Wider patches
+// there keep the check per pixel: 13 x 13 in the six-wave shape would spill, and a
+// dense cloud on a border, most of whose pixels the check saves, takes 855 us with
+// 25 x 25 patches and took 966 with the columns clamped.
 template <int P>
 __device__ __forceinline__ void patch_global(const float* __restrict__ obs, int u0, int v0,
                                              int W, int H, double bsub, const double (&gx)[P],
                                              double gy, double by, const double* gstep,
                                              double& X, double& G2y, double& sd2) {
-  if constexpr (P < kFusedMaxP) {
-    const bool inside = u0 >= 0 && v0 >= 0 && u0 <= W - P && v0 <= H - P;
-    if ((int64_t)W * H <= (int64_t)1 << 30 && __ballot(!inside) == 0) {  // byte offsets of 32 bits
-      uint32_t at = 4u * ((uint32_t)v0 * (uint32_t)W + (uint32_t)u0);
+  constexpr int C = P <= 7 ? P : P == 11 ? 6 : 5;
+  const bool inside = u0 >= 0 && v0 >= 0 && u0 <= W - P && v0 <= H - P;
+  if ((int64_t)W * H <= (int64_t)1 << 30) {  // byte offsets of 32 bits
+    const char* const base = reinterpret_cast<const char*>(obs);
+    uint32_t at = 4u * ((uint32_t)v0 * (uint32_t)W);  // modulo 2^32 above the frame
+    if (__ballot(!inside) == 0) {
+      at += 4u * (uint32_t)u0;
 #pragma unroll 1
       for (int dy = 0; dy < P; ++dy) {
-        float z[P];
-#pragma unroll
-        for (int dx = 0; dx < P; ++dx)
-          z[dx] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(obs + dx) + at);
         double rd = 0.0;
 #pragma unroll
-        for (int dx = 0; dx < P; ++dx) {
-          const double d = (double)z[dx] - bsub;
-          rd = dx == 0 ? d : fma(d, gx[dx], rd);
-          sd2 = fma(d, d, sd2);
+        for (int d0 = 0; d0 < P; d0 += C) {
+          float z[C];
+#pragma unroll
+          for (int dx = d0; dx < min(d0 + C, P); ++dx)
+            z[dx - d0] = *reinterpret_cast<const float*>(base + 4 * dx + at);
+#pragma unroll
+          for (int dx = d0; dx < min(d0 + C, P); ++dx) {
+            const double d = (double)z[dx - d0] - bsub;
+            rd = dx == 0 ? d : fma(d, gx[dx], rd);
+            sd2 = fma(d, d, sd2);
+          }
+          if (C < P) __builtin_amdgcn_sched_barrier(0);  // z's registers are the next ones'
+        }
+        X = fma(gy, rd, X);
+        G2y = fma(gy, gy, G2y);
+        gy *= gstep[dy] * by;
+        at += 4u * (uint32_t)W;
+      }
+      return;
+    }
+    if constexpr (P < kFusedMaxP) {
+      uint32_t some = 0;  // bit d0 / C: a patch of the wave has one of these columns inside
+#pragma unroll
+      for (int d0 = 0; d0 < P; d0 += C)
+        if (__ballot(u0 + min(d0 + C, P) > 0 && u0 + d0 < W) != 0) some |= 1u << (d0 / C);
+#pragma unroll 1
+      for (int dy = 0; dy < P; ++dy) {
+        double rd = 0.0;
+        if ((unsigned)(v0 + dy) < (unsigned)H && u0 > -P && u0 < W) {
+#pragma unroll
+          for (int d0 = 0; d0 < P; d0 += C) {
+            if (!(some >> (d0 / C) & 1)) continue;  // uniform in the wave
+            float z[C];
+#pragma unroll
+            for (int dx = d0; dx < min(d0 + C, P); ++dx)
+              z[dx - d0] = *reinterpret_cast<const float*>(
+                  base + (at + 4u * (uint32_t)min(max(u0 + dx, 0), W - 1)));
+#pragma unroll
+            for (int dx = d0; dx < min(d0 + C, P); ++dx) {
+              const double d =
+                  (unsigned)(u0 + dx) < (unsigned)W ? (double)z[dx - d0] - bsub : 0.0;
+              rd = fma(d, gx[dx], rd);  // (gx[0] = 1)
+              sd2 = fma(d, d, sd2);
+            }
+            if (C < P) __builtin_amdgcn_sched_barrier(0);
+          }
         }
         X = fma(gy, rd, X);
         G2y = fma(gy, gy, G2y);
@@ -1084,23 +1131,41 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
   // that is too small (a workgroup whose particles form clusters, as at a jump
   // of the Z order), each wave keeps its own box in a quarter of it, and a
   // wave whose box still does not fit reads the frame. The sums are taken in
-  // the frame path's order, so the choice moves no bit. The frame path is
-  // bound by its loads: P^2 bounds-checked ones per particle, 64 addresses
-  // each. Measured: the first frame of 250,007 particles with 25 x 25 patches
-  // from a Gaussian prior 278 -> 67 us; a step of 2^20 particles that lost the
-  // spot (9 x 9) 44.5 -> 34.7 us. Gradient mode keeps the two choices: a third
-  // cost its kernel 2 % (registers) on clouds that never need it. So do patches up to
-  // 3 x 3, and 5 x 5 and 7 x 7 where the box lies in the frame (patch_global then
-  // has its quick form): staging takes more loads than reading their pixels (2^22
-  // particles spread over 68 x 68 pixels, staged and from the frame: a step 1 x 1 138 and
-  // 85 us, 3 x 3 149 and 98, 5 x 5 157 and 121, 7 x 7 170 and 141, 9 x 9 187 and 189; over
-  // 44 x 44 pixels 5 x 5 125 and 107, 7 x 7 139 and 121, 9 x 9 162 and 166).
+  // the frame path's order, so the choice moves no bit. Over a border of the frame
+  // a box is staged only whole, and only if its particles fill it: where they do
+  // not, the waves' own boxes are small, so that the loads of each meet few lines,
+  // and those of patches outside the frame are left out. The waves' boxes together
+  // have to cover the workgroup's twice (four times in a box that is filled): 3.2
+  // million particles around the middle column of a 96 x 512 frame, 60 pixels to a
+  // standard deviation, with every box staged and with this rule 11 x 11 patches 116
+  // and 79 us, 15 x 15 151 and 141; 2^21 particles that fill 44 x 44 pixels on a
+  // corner, staged and from the frame, 11 x 11 102 and 130 us. Inside, 2^20 particles
+  // in four clusters to a workgroup, staged and from the frame, in a box that fits
+  // 25 x 25 169 and 237 us, wave by wave 111 and 237. Patches up to 3 x 3 are not
+  // staged, nor 5 x 5, nor 7 x 7 where the box lies in the frame: staging takes more
+  // loads than reading their pixels (2^22 particles spread over 68 x 68 pixels, staged
+  // and from the frame: a step 1 x 1 138 and 85 us, 3 x 3 149 and 98, 5 x 5 157 and
+  // 121, 7 x 7 170 and 141, 9 x 9 187 and 189). Gradient mode keeps the two choices: a
+  // third cost its kernel 2 % (registers) on clouds that never need it.
   constexpr int kAll = TILE + kSq;
   enum { kFrame, kFloat, kDouble };
   int single = kFrame;  // uniform in a wave
   int sx0 = tx0, sy0 = ty0, sw = 0, sbase = 0;
   const bool inside = tx0 >= 0 && ty0 >= 0 && mxx < m.W - h && mxy < m.H - h;
-  if (!GRAD && !use_lds && (P >= 9 || (P >= 5 && !inside))) {
+  bool stage = P >= 9 && inside;  // uniform in the workgroup
+  if (!GRAD && !use_lds && P >= 7 && !inside && tw64 * th64 <= 2 * kAll) {
+    int own = 0;  // pixels of the waves' boxes
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int x0 = __builtin_amdgcn_readfirstlane(ish[i]);
+      const int x1 = __builtin_amdgcn_readfirstlane(ish[4 + i]);
+      const int y0 = __builtin_amdgcn_readfirstlane(ish[8 + i]);
+      const int y1 = __builtin_amdgcn_readfirstlane(ish[12 + i]);
+      own += (x1 - x0 + P) * (y1 - y0 + P);
+    }
+    stage = own >= 2 * tw * th;
+  }
+  if (!GRAD && !use_lds && stage) {
     int64_t bw = tw64, bh = th64, cap = kAll;
     int e0 = t, step = 256;
     if (bw * bh > 2 * (int64_t)kAll) {  // uniform in the workgroup
@@ -1250,6 +1315,9 @@ __device__ __forceinline__ void step_spot(const Model& m, const Buffers& b,
     const double ssq = sd2 - 2.0 * I * X + I * I * (G2x * G2y);
     l = prior_lw(m, b, cur, mode, cdelta, amv, base + ta) - ssq * m.inv2sig2 - m.lognorm_obs;
   }
+  // the MMSE sums convert the state anew: kept in doubles since the patch's centre was
+  // taken, it would be the registers that the widest fused patch lacks
+  if constexpr (P == kFusedMaxP && !GRAD) asm("" : "+v"(o.x), "+v"(o.y));
   const double e = finish_block(b, cur, blk, active, l, o, tile, dsh, L.ksh);
   if constexpr (GRAD) {
     // the block's sum_i E_i d l_i / d theta, weighted like the MMSE sums and
