@@ -555,7 +555,7 @@ int ppf_step_batched(ppf_batch h, const float* obs_dev);
  * of a batched step (one step launch for all patch sizes up to 13, or two, one
  * per wider size, then the merge and resampling launches), with the step
  * launches side by side. Replayed are steps of more than 12 launches, and those
- * of six or more step launches that take 4096 workgroups (2^20 particles) or
+ * of four or more step launches that take 4096 workgroups (2^20 particles) or
  * more. */
 int ppf_batch_set_graph(ppf_batch h, int enable);
 int ppf_batch_graph_launches(ppf_batch h, int32_t* launches);

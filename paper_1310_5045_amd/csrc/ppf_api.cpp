@@ -466,14 +466,15 @@ struct Runner {
   // - for a batch with kGraphGroup step launches or more (one for all patch
   //   sizes up to 13, or two, and one per wider size) of kGraphGroupBlocks
   //   workgroups in all: the graph runs them side by side, so that one's last
-  //   workgroups do not leave the chip idle. A track of 200,000 particles per
-  //   size, launched and replayed: 5 launches 103 / 103 us, 6 launches 119 /
-  //   105, 7 launches 146 / 123, 8 launches 151 / 141. Of 50,000 (1200 to 2000
-  //   workgroups) 64 / 74, 70 / 75, 82 / 81 and 88 / 78, of 2000 61 / 66, 63 /
-  //   71, 76 / 76 and 82 / 87. With 4 launches the two are within 3 % from
-  //   300,000 particles on, with fewer a replay is slower.
+  //   workgroups do not leave the chip idle. A fused and three wide launches over
+  //   40 tracks of unequal sizes, launched and replayed: 1.3 million particles 240 /
+  //   179 us, 2.2 million 383 / 318, 7 million 530 / 434. A track of 200,000
+  //   particles per size: 5 launches 103 / 103 us, 6 launches 119 / 105, 7 launches
+  //   146 / 123, 8 launches 151 / 141. Of 50,000 (1200 to 2000 workgroups) 64 / 74,
+  //   70 / 75, 82 / 81 and 88 / 78, of 2000 61 / 66, 63 / 71, 76 / 76 and 82 / 87.
+  //   With 3 launches and fewer a replay is slower.
   static constexpr size_t kGraphLaunches = 12;
-  static constexpr size_t kGraphGroup = 6;
+  static constexpr size_t kGraphGroup = 4;
   static constexpr int64_t kGraphGroupBlocks = 4096;
   static bool replay_pays(const ppf::StepGraph& g) {
     return g.launches() > kGraphLaunches ||

@@ -1,5 +1,5 @@
 """Steps that graph mode replays: RPA over more sorted lists than are ranked by counting
-(many launches), and batches with six or more step launches of 4096 workgroups or more
+(many launches), and batches with four or more step launches of 4096 workgroups or more
 (their step launches side by side). Each test asks which way its steps run, and every
 replay gives bit for bit what a plainly stepped twin gives, with host work and
 synchronisation between the replays, the frames in alternating buffers, and a reset."""
@@ -77,7 +77,8 @@ def test_rpa(ppf, movie, groups, dlb, replayed):
     (range(15, 26, 2), 0, 180_000, True),    # six wide sizes
     (range(9, 26, 2), 2, 117_000, True),     # two fused launches and six wide sizes
     (range(15, 26, 2), 0, 170_000, False),   # too few workgroups
-    (range(17, 26, 2), 0, 300_000, False),   # five launches
+    (range(19, 26, 2), 0, 263_000, True),    # four wide sizes
+    (range(21, 26, 2), 0, 400_000, False),   # three launches
 ])
 def test_batch_over_many_sizes(ppf, movie, sizes, shapes, n, replayed):
     ps = spots(ppf, sizes, n)
